@@ -263,7 +263,8 @@ pf_status phasefield_velocity_coeffs_grad(const pf_params *p, int32_t modes,
  * ("tiled": one launch per RK stage; "fused": two stages per launch; "global": one thread per
  * cell), the column tile (x by y) and, when it ends in a third number, the planes per z-chunk;
  * without one, each launch chooses the chunk length for the grid and the device's resident
- * workgroups. "_big" forces the addressing form of arrays of 4 GiB or more. */
+ * workgroups. "fused_brick" variants run two stages per launch on bricks (x by y by z) without a
+ * march; "fused_plane" a whole step per launch on one-plane grids (bricks on thicker ones). "_big" forces the addressing form of arrays of 4 GiB or more. */
 int32_t phasefield_variant_count(int32_t dtype);
 
 /* Short name of a variant (static string), or NULL if out of range. */
@@ -278,12 +279,14 @@ const char *phasefield_variant_name(int32_t dtype, int32_t variant);
  * per entry: dtype nx ny nz variant-name). Without a cached choice, create picks a default from
  * the grid size and dtype (fused sweeps from about 104^3 cells in FP32 and 128^3 in FP64,
  * per-stage kernels below and on every grid of one plane; both with per-launch chunk
- * lengths); a grid with walls takes the per-stage kernel in FP64 and, in FP32, the fused 32x16
+ * lengths; whole steps of small and one-plane grids as phasefield_solver_variant says); a grid with walls takes the per-stage kernel in FP64 and, in FP32, the fused 32x16
  * sweeps from about 144^3 cells (per-stage below). */
 pf_status phasefield_autotune(pf_solver *s, int32_t reps, int32_t *best, double *times_ms,
                               void *hip_stream);
 
-/* The variant a handle runs. */
+/* The variant a handle runs: its stage kernel, and whole steps too, except that a handle created
+ * with variant -1 (and no tuned choice for its grid) runs whole steps of small grids in bricks
+ * (RK4, RK2) and of one-plane grids in one launch each (RK4, RK3, RK2), with identical results. */
 int32_t phasefield_solver_variant(const pf_solver *s);
 
 /* ----------------------------------------------------------------------------------------

@@ -206,6 +206,19 @@ int pf::default_variant(const pf_params& p)
     return wall_mask(p) != 0 ? walled_default_variant(p.dtype, p.n) : tuned_variant(p.dtype, p.n);
 }
 
+int pf::step_variant(const pf_params& p, int variant)
+{
+    if (p.variant >= 0) return variant;
+    const int wm = wall_mask(p);
+    if (wm == 0) {
+        std::lock_guard<std::mutex> lk(g_tune_mu);
+        load_tune_cache_locked();
+        if (g_tuned.count(std::make_tuple(p.dtype, p.n[0], p.n[1], p.n[2]))) return variant;
+    }
+    const int v = small_step_variant(p.n[0], p.n[1], p.n[2], p.dtype, p.scheme, wm != 0);
+    return v >= 0 ? v : variant;
+}
+
 static void store_tuned(int dtype, const int32_t n[3], int v)
 {
     std::lock_guard<std::mutex> lk(g_tune_mu);
@@ -252,6 +265,7 @@ extern "C" pf_status phasefield_create(const pf_params* p, pf_solver** out)
     s->N = (size_t)p->n[0] * p->n[1] * p->n[2];
     s->esz = p->dtype == PF_F32 ? sizeof(float) : sizeof(double);
     s->variant = p->variant >= 0 ? p->variant : default_variant(*p);
+    s->step_variant = step_variant(*p, s->variant);
     hipError_t e = hipSuccess;
     for (void** b : {&s->ya, &s->yb, &s->acc}) {
         e = hipMalloc(b, s->N * s->esz);
@@ -612,6 +626,47 @@ static hipError_t enqueue_step_fused(const pf_params& p, int variant, const T* p
     return run_fused_sweep<T>(variant, b, true, st);
 }
 
+// Arguments of a whole step of a one-plane grid from time t (stage_plane.hip); the coefficients
+// and stage times of enqueue_step.
+template <typename T>
+static PlaneStepArgs<T> make_plane_step(const pf_params& p, double t, const T* phi, T* out,
+                                        const T* U, const T* V, const T* W)
+{
+    const double dt = p.dt;
+    PlaneStepArgs<T> a;
+    a.phi = phi;
+    a.out = out;
+    a.U = U;
+    a.V = V;
+    a.W = W;
+    a.nx = p.n[0];
+    a.ny = p.n[1];
+    a.inv_2dx = (T)(1.0 / (2.0 * p.dx));
+    a.ge = (T)(p.gamma * p.eps / (p.dx * p.dx));
+    a.hg = (T)(0.5 * p.gamma / p.dx);
+    a.delta2 = (T)(p.delta * p.delta);
+    a.walls = wall_mask(p);
+    double ts[4] = {t, t + 0.5 * dt, t + 0.5 * dt, t + dt};
+    double c[4] = {0.5 * dt, 0.5 * dt, dt, 0.0}, b[4] = {dt / 6.0, dt / 3.0, dt / 3.0, dt / 6.0};
+    if (p.scheme == PF_RK3) {
+        constexpr double g1 = 8.0 / 15.0, g2 = 5.0 / 12.0, g3 = 0.75, z2 = -17.0 / 60.0;
+        ts[1] = t + g1 * dt;
+        ts[2] = t + (g1 + g2 + z2) * dt;
+        c[0] = dt * g1;
+        c[1] = dt * g2;
+        b[0] = dt * (g1 + z2);
+        b[2] = dt * g3;
+    } else if (p.scheme == PF_RK2) {
+        b[1] = dt;
+    }
+    for (int s = 0; s < 4; ++s) {
+        a.nhs[s] = (T)(-0.5 * time_factor(p, ts[s]) / p.dx);
+        a.c[s] = (T)c[s];
+        a.b[s] = (T)b[s];
+    }
+    return a;
+}
+
 // nsteps steps from t0 (step m at t0 + m dt), phi updated in place. A fused variant alternates
 // phi between the caller's buffer and acc; after an odd count RK4 runs its last step in place
 // (through a copy of phi in ya), RK2 copies back.
@@ -627,6 +682,9 @@ hipError_t pf::enqueue_steps(const pf_params& p, int variant, T* phi, const T* U
     const bool fused = (p.scheme == PF_RK4 || p.scheme == PF_RK2) && variant_is_fused(dtype, variant) &&
                        !(wm != 0 && field_needs_big(p.n[0], p.n[1], p.n[2], sizeof(T))) &&
                        !(nu && nu->on());
+    // one-plane grids of a variant that runs a whole step per launch: phi and acc alternate
+    const bool plane = p.n[2] == 1 && stage_variant(dtype, variant).plane && p.scheme != PF_EULER &&
+                       !(nu && nu->on());
     T* cur = phi;
     for (int m = 0; m < nsteps; ++m) {
         const double t = t0 + (double)m * p.dt;
@@ -637,6 +695,11 @@ hipError_t pf::enqueue_steps(const pf_params& p, int variant, T* phi, const T* U
             T* next = cur == phi ? acc : phi;
             e = run_stage<T>(variant, make_stage<T>(p, time_factor(p, t), cur, nullptr, cur, nullptr,
                                                     next, 0.0, p.dt, U, V, W, nu), st);
+            cur = next;
+        } else if (plane) {
+            T* next = cur == phi ? acc : phi;
+            e = launch_plane_step<T>(make_plane_step<T>(p, t, cur, next, U, V, W),
+                                     p.scheme == PF_RK4 ? 4 : p.scheme == PF_RK3 ? 3 : 2, st);
             cur = next;
         } else if (fused) {
             if (m == nsteps - 1 && cur == phi && p.scheme == PF_RK4) {
@@ -671,7 +734,7 @@ static pf_status capture_steps(pf_solver* s, T* phi, const T* U, const T* V, con
     release_graph(g);
     hipError_t e = hipStreamBeginCapture(st, hipStreamCaptureModeThreadLocal);
     if (e != hipSuccess) return hip_fail(e, "phasefield_step: begin capture");
-    const hipError_t le = enqueue_steps<T>(s->p, s->variant, phi, U, V, W, (T*)s->ya, (T*)s->yb,
+    const hipError_t le = enqueue_steps<T>(s->p, s->step_variant, phi, U, V, W, (T*)s->ya, (T*)s->yb,
                                            (T*)s->acc, t0, nsteps, st, &s->nu);
     hipGraph_t graph = nullptr;
     e = hipStreamEndCapture(st, &graph);
@@ -693,7 +756,7 @@ static pf_status capture_steps(pf_solver* s, T* phi, const T* U, const T* V, con
     g.V = V;
     g.W = W;
     g.stream = st;
-    g.variant = s->variant;
+    g.variant = s->step_variant;
     g.t0 = t0;
     g.nsteps = nsteps;
     return PF_OK;
@@ -709,7 +772,7 @@ static pf_status step_impl(pf_solver* s, T* phi, const T* U, const T* V, const T
     const bool graphs = p.use_graph && st != nullptr;
     auto same_operands = [&]() {
         return g.exec && g.phi == phi && g.U == U && g.V == V && g.W == W && g.stream == st &&
-               g.variant == s->variant;
+               g.variant == s->step_variant;
     };
     if (graphs && p.vel_mode != PF_VEL_STEADY && nsteps >= kLoopGraphMin &&
         nsteps <= kLoopGraphMax) {
@@ -735,7 +798,7 @@ static pf_status step_impl(pf_solver* s, T* phi, const T* U, const T* V, const T
         }
     }
     if (done < nsteps) {
-        hipError_t e = enqueue_steps<T>(p, s->variant, phi, U, V, W, (T*)s->ya, (T*)s->yb,
+        hipError_t e = enqueue_steps<T>(p, s->step_variant, phi, U, V, W, (T*)s->ya, (T*)s->yb,
                                         (T*)s->acc, t0 + (double)done * p.dt, nsteps - done, st,
                                         &s->nu);
         if (e != hipSuccess) return hip_fail(e, "phasefield_step: launch");
@@ -767,10 +830,11 @@ extern "C" pf_status phasefield_step(pf_solver* s, void* phi, const void* u, con
 // reads (scheme_stage_count), the new phi into phi_next (phi itself: in place): the per-stage
 // launches with the stage outputs directed into the caller's buffers; an RK4 step of a fused
 // variant (no walls; FP64 from 176^3 cells, where the fused sweeps overtake the per-stage
-// launches) runs its two sweeps, each storing its middle value (y2, y4; sweep A also writes y3),
-// when out of place, and in place sweep A then two per-stage launches for y4 and the new phi;
-// on a non-uniform mesh the per-stage launches of that mesh's kernel. Every form rounds alike, so the new phi and the stages are bit-identical to those of
-// phasefield_step and of the adjoint's own recompute.
+// launches), or of a grid whose steps run in bricks, runs its two sweeps, each storing its middle
+// value (y2, y4; sweep A also writes y3), when out of place, and in place sweep A then two
+// per-stage launches for y4 and the new phi; on a non-uniform mesh the per-stage launches of that
+// mesh's kernel. Every form rounds alike, so the new phi and the stages are bit-identical to those
+// of phasefield_step and of the adjoint's own recompute.
 template <typename T>
 static hipError_t step_stages_impl(pf_solver* s, const T* phi, T* phi_next, const T* U,
                                    const T* V, const T* W, double t, T* y2, T* y3, T* y4,
@@ -810,23 +874,25 @@ static hipError_t step_stages_impl(pf_solver* s, const T* phi, T* phi_next, cons
                             st);
     }
     const long long cells = (long long)p.n[0] * p.n[1] * p.n[2];
-    const bool fused = !nu && variant_is_fused(p.dtype, v) && wall_mask(p) == 0 &&
-                       (p.dtype == PF_F32 || cells >= 176LL * 176 * 176);
+    const int sv = s->step_variant;
+    const bool brick = stage_variant(p.dtype, sv).brick;  // walls too; one plane: single stages
+    const bool fused = !nu && variant_is_fused(p.dtype, sv) && (brick ? p.n[2] > 1 : wall_mask(p) == 0) &&
+                       (p.dtype == PF_F32 || brick || cells >= 176LL * 176 * 176);
     if (fused && phi_next != phi) {
         // out of place: the two sweeps of the step, the accumulator in phi_next (sweep B writes
         // the new phi over it at the cell), sweep A storing y2, sweep B y4
         FusedArgs<T> a = make_fused<T>(p, false, t, phi, phi_next, U, V, W, y3);
         a.out_mid = y2;
-        e = run_fused_sweep<T>(v, a, false, st);
+        e = run_fused_sweep<T>(sv, a, false, st);
         if (e != hipSuccess) return e;
         FusedArgs<T> b = make_fused<T>(p, true, t, phi, phi_next, U, V, W, y3);
         b.out_mid = y4;
-        return run_fused_sweep<T>(v, b, true, st);
+        return run_fused_sweep<T>(sv, b, true, st);
     }
     if (fused) {
         FusedArgs<T> a = make_fused<T>(p, false, t, phi, acc, U, V, W, y3);
         a.out_mid = y2;
-        e = run_fused_sweep<T>(v, a, false, st);
+        e = run_fused_sweep<T>(sv, a, false, st);
     } else {
         e = run_stage<T>(v, make_stage<T>(p, time_factor(p, t), phi, phi, phi, y2, acc, 0.5 * dt,
                                           dt / 6.0, U, V, W, nu), st);
@@ -979,7 +1045,7 @@ static pf_status autotune_impl(pf_solver* s, int reps, int32_t* best, double* ti
     for (T* b : {phi, U, V, W})
         if (b) (void)hipFree(b);
     if (ret == PF_OK) {
-        s->variant = best_v;
+        s->variant = s->step_variant = best_v;
         if (wall_mask(p) == 0) store_tuned(p.dtype, p.n, best_v);  // the cache is for periodic grids
         release_graph(s->graph);
         if (best) *best = best_v;

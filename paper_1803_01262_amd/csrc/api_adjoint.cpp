@@ -206,7 +206,9 @@ static pf_status adjoint_impl(pf_solver* s, const T* phi, const T* U, const T* V
     // no accumulator output; FP64 adjoint step against three per-stage launches on 64x8 tiles:
     // 128^3 0.259 / 0.259 ms, 256^3 1.90 / 1.95, 512^3 14.98 / 15.38); on walled grids three
     // per-stage launches.
-    const bool fused_rc = !nu && variant_is_fused(p.dtype, v) && wall_mask(p) == 0;
+    const int sv = s->step_variant;
+    const bool brick_rc = stage_variant(p.dtype, sv).brick && p.n[2] > 1;  // bricks take walls
+    const bool fused_rc = !nu && (brick_rc || (variant_is_fused(p.dtype, v) && wall_mask(p) == 0));
     const int vs = variant_is_fused(p.dtype, v) && !fused_rc ? stage_variant_index(p.dtype, "tiled_64x8") : v;
     if (stages) {
         y2 = (T*)stages[0];
@@ -217,7 +219,7 @@ static pf_status adjoint_impl(pf_solver* s, const T* phi, const T* U, const T* V
         FusedArgs<T> a = make_fused<T>(p, false, t, phi, y4, U, V, W, y3);
         a.out_mid = y2;
         a.out_acc = nullptr;
-        e = run_fused_sweep<T>(v, a, false, st);
+        e = run_fused_sweep<T>(brick_rc ? sv : v, a, false, st);
     } else {
         e = run_stage<T>(vs, make_stage<T>(p, s1, phi, phi, nullptr, y2, nullptr, 0.5 * dt, 0.0, U, V, W, nu), st);
         if (e == hipSuccess)

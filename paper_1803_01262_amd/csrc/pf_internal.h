@@ -141,6 +141,22 @@ struct FusedArgs {
     int walls;                  // bit a: axis a walled
 };
 
+// A whole RK step of a one-plane grid (stage_plane.hip): phi -> out (another array). Stage s runs at
+// nhs[s]; y = phi + c[s] f (RK3's second: acc + c[1] f), acc += b[s] f, the new phi acc + b[last] f
+// (RK2: phi + b[1] f).
+template <typename T>
+struct PlaneStepArgs {
+    const T* phi;
+    T* out;
+    const T* U;
+    const T* V;
+    const T* W;
+    int nx, ny;
+    T inv_2dx, ge, hg, delta2;  // as in StageArgs
+    T nhs[4], c[4], b[4];
+    int walls;
+};
+
 // An array of nx*ny*nz elements of `es` bytes needs the per-plane buffer descriptors of the
 // z-marches (buffer offsets are 32-bit) when it spans 4 GiB or more.
 inline bool field_needs_big(int nx, int ny, int nz, size_t es)
@@ -184,6 +200,13 @@ int resident_groups_per_cu(const void* kernel, int threads);
 // current device (march_chunk_planes with the device's resident slots); 0 on error.
 int launch_chunk_planes(const void* kernel, int threads, long long tiles, int nz, int extra);
 
+// The launchers of the fused two-stage sweeps: the z-marches (pf_fused_launch.h) and the bricks
+// (stage_brick.hip).
+template <typename T, int TX, int TY, int KZ, bool FORCE_BIG>
+hipError_t launch_fused(const FusedArgs<T>& a, bool sweep_b, hipStream_t st);
+template <typename T, int BX, int BY, int BZ, int NT>
+hipError_t launch_brick(const FusedArgs<T>& a, bool sweep_b, hipStream_t st);
+
 // ------------------------------------------------------------------ stage-kernel variants
 // Either a per-stage kernel (four launches per RK4 step) or a fused pair of sweeps (two
 // launches per RK4 step). Every variant produces bit-identical results.
@@ -193,12 +216,19 @@ struct StageVariant {
     hipError_t (*launch_f64)(const StageArgs<double>&, hipStream_t);
     hipError_t (*fused_f32)(const FusedArgs<float>&, bool sweep_b, hipStream_t);  // fused
     hipError_t (*fused_f64)(const FusedArgs<double>&, bool sweep_b, hipStream_t);
+    bool brick = false;  // the fused form is a brick (stage_brick.hip), not a march
+    bool plane = false;  // on one-plane grids, a whole step per launch (stage_plane.hip)
 };
 // Variants available for a storage dtype, indexed 0..count-1 (per dtype).
 int stage_variant_count(int dtype);
 const StageVariant& stage_variant(int dtype, int v);
 bool variant_is_fused(int dtype, int v);
+// A step of a one-plane grid in one launch, `stages` (4, 3 or 2) RK stages.
+template <typename T>
+hipError_t launch_plane_step(const PlaneStepArgs<T>& a, int stages, hipStream_t st);
 int default_stage_variant(int nx, int ny, int nz, int dtype);
+// The brick variant for whole steps of a small grid, or -1: its stage variant's own step.
+int small_step_variant(int nx, int ny, int nz, int dtype, int scheme, bool walls);
 // The per-stage variant that single stages of a fused solver run on (adjoint recompute, Euler).
 int per_stage_variant(int nx, int ny, int nz, int dtype);
 // Index of the variant of that name (0 if there is none).

@@ -180,8 +180,6 @@ hipError_t launch_stage_tiled(const StageArgs<T>& a, hipStream_t st)
 
 template <typename T>
 hipError_t launch_stage_global(const StageArgs<T>& a, hipStream_t st);
-template <typename T, int TX, int TY, int KZ, bool FORCE_BIG>
-hipError_t launch_fused(const FusedArgs<T>& a, bool sweep_b, hipStream_t st);
 
 #define PF_TILED(TX, TY, KZ)                                                            \
     {"tiled_" #TX "x" #TY "x" #KZ, launch_stage_tiled<float, TX, TY, KZ, false>,        \
@@ -199,6 +197,10 @@ hipError_t launch_fused(const FusedArgs<T>& a, bool sweep_b, hipStream_t st);
 #define PF_FUSED32(TX, TY, KZ)                                                          \
     {"fused_" #TX "x" #TY "x" #KZ, nullptr, nullptr,                                    \
      launch_fused<float, TX, TY, KZ, false>, nullptr}
+
+#define PF_BRICK(NAME, BX, BY, BZ, NT)                                                  \
+    {NAME, nullptr, nullptr, launch_brick<float, BX, BY, BZ, NT>,                       \
+     launch_brick<double, BX, BY, BZ, NT>, true}
 
 static const StageVariant kVariants[] = {
     PF_TILED(64, 8, 16),
@@ -228,6 +230,12 @@ static const StageVariant kVariants[] = {
      launch_stage_tiled<double, 64, 8, 16, true>, nullptr, nullptr},
     {"fused_64x8x32_big", nullptr, nullptr, launch_fused<float, 64, 8, 32, true>,
      launch_fused<double, 64, 8, 32, true>},
+    PF_BRICK("fused_brick8x8x8", 8, 8, 8, 1024),
+    PF_BRICK("fused_brick8x8x4", 8, 8, 4, 512),
+    {"fused_brick16x8x8", nullptr, nullptr, launch_brick<float, 16, 8, 8, 1024>, nullptr, true},
+    // one-plane grids: a whole step per launch (thicker grids run the small bricks)
+    {"fused_plane", nullptr, nullptr, launch_brick<float, 8, 8, 4, 512>,
+     launch_brick<double, 8, 8, 4, 512>, true, true},
 };
 constexpr int kNumVariants = (int)(sizeof(kVariants) / sizeof(kVariants[0]));
 
@@ -332,6 +340,34 @@ int default_stage_variant(int nx, int ny, int nz, int dtype)
                    : per_stage_variant(nx, ny, nz, dtype);
     return cells >= kFusedMinCellsF64 ? variant_by_name(dtype, "fused_32x16")
                                       : per_stage_variant(nx, ny, nz, dtype);
+}
+
+// Whole RK4 and RK2 steps of small grids (and RK3 of one-plane grids): a brick variant, or -1 where
+// the grid's stage variant serves them. One brick per compute unit takes one latency however few
+// cells it has, so the smallest brick that needs at most one per unit wins (MI355X, us per RK4
+// step, per-stage launches / 8x8x4 / 8x8x8 / 16x8x8 bricks: FP32 32^3 27.7 / 11.0 / 13.0 / 14.7,
+// 48^3 28.7 / 14.5 / 13.3 / 15.7, 64^3 29.4 / 23.7 / 20.3 / 16.7, 80^3 35.1 / 33.3 / 30.0 / 25.1,
+// 96^3 40.0 / 53 / 48 / 39.1; FP64 32^3 29.7 / 13.5 / 16.1, 48^3 33.8 / 20.4 / 17.7, 56^3 34.6 /
+// 28.5 / 31.7, 64^3 35.0 / 34.6 / 32.3, 80^3 42 / 59 / 60). From there up the halos that every
+// brick evaluates again cost more than the launches they save; element-wise loads (walls, odd
+// rows) reach that point earlier (FP32 16x8x8 bricks, walls on x and z: 64^3 20.5 against 33.2,
+// 80^3 36.9 against 39.6, 96^3 70 against 45).
+int small_step_variant(int nx, int ny, int nz, int dtype, int scheme, bool walls)
+{
+    if (scheme == PF_EULER) return -1;
+    if (nz == 1) return variant_by_name(dtype, "fused_plane");
+    if (scheme == PF_RK3) return -1;
+    auto bricks = [&](int bx, int by, int bz) {
+        return (long long)((nx + bx - 1) / bx) * ((ny + by - 1) / by) * ((nz + bz - 1) / bz);
+    };
+    if (bricks(8, 8, 4) <= 256) return variant_by_name(dtype, "fused_brick8x8x4");
+    if (bricks(8, 8, 8) <= 256) return variant_by_name(dtype, "fused_brick8x8x8");
+    if (dtype == PF_F32) {
+        const bool pieces = !walls && nx % 4 == 0;
+        return bricks(16, 8, 8) <= (pieces ? 768 : 512) ? variant_by_name(dtype, "fused_brick16x8x8") : -1;
+    }
+    if (bricks(8, 8, 4) <= 768) return variant_by_name(dtype, "fused_brick8x8x4");
+    return bricks(8, 8, 8) <= 512 ? variant_by_name(dtype, "fused_brick8x8x8") : -1;
 }
 
 // FP32 on 64x4 tiles unless those pad more columns than 32x4 (512^3: 3.36 ms per RK4 step against
