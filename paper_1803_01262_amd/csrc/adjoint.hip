@@ -212,7 +212,7 @@ __global__ void __launch_bounds__(TX* TY) adjoint_tiled_kernel(AdjArgs<T> a, int
         for (int s = 0; s < NL; ++s)
             if (lpos[s] >= 0) {
                 pre_y[s] = fy.load(kw, loff[s]);
-                pre_k[s] = a.kap_scale * fk.load(kw, loff[s]);
+                pre_k[s] = fk.load(kw, loff[s]);  // scaled at the commit: no wait for the load here
             }
     };
     auto commit = [&](int slot) {
@@ -220,7 +220,7 @@ __global__ void __launch_bounds__(TX* TY) adjoint_tiled_kernel(AdjArgs<T> a, int
         for (int s = 0; s < NL; ++s)
             if (lpos[s] >= 0) {
                 sy[slot * PS + lpos[s]] = pre_y[s];
-                sk[slot * PS + lpos[s]] = pre_k[s];
+                sk[slot * PS + lpos[s]] = a.kap_scale * pre_k[s];
             }
     };
     int h_o = -1, h_dst = 0, h_axis = 0;

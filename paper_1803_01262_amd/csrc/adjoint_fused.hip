@@ -178,7 +178,7 @@ adjoint_pair_kernel(AdjPairArgs<T> a, int tiles_x, int tiles_y, int kz)
         for (int s = 0; s < NLI; ++s)
             if (li_pos[s] >= 0) {
                 pre_yh[s] = fyh.load(kw, li_off[s]);
-                pre_kh[s] = a.kscaleH * fsrc.load(kw, li_off[s]);
+                pre_kh[s] = fsrc.load(kw, li_off[s]);  // scaled at the commit: no wait here
             }
     };
     auto commit_in = [&](int slot) {
@@ -186,7 +186,7 @@ adjoint_pair_kernel(AdjPairArgs<T> a, int tiles_x, int tiles_y, int kz)
         for (int s = 0; s < NLI; ++s)
             if (li_pos[s] >= 0) {
                 s_yh[slot * INS + li_pos[s]] = pre_yh[s];
-                s_kh[slot * INS + li_pos[s]] = pre_kh[s];
+                s_kh[slot * INS + li_pos[s]] = a.kscaleH * pre_kh[s];
             }
     };
     auto fetch_mid = [&](int kyl, int klp) {
