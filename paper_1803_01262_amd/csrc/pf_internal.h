@@ -280,6 +280,10 @@ template <typename T>
 hipError_t launch_adjoint_stage_global(const AdjArgs<T>& a, hipStream_t st);  // one thread per cell
 template <typename T>
 hipError_t launch_adjoint_stage_nu(const AdjArgs<T>& a, hipStream_t st);  // non-uniform mesh
+// One reverse stage on bricks (adjoint_brick.hip). Uniform meshes, arrays below 4 GiB.
+template <typename T>
+hipError_t launch_adjoint_brick(const AdjArgs<T>& a, hipStream_t st);
+bool adjoint_takes_bricks(int nx, int ny, int nz, int dtype);
 // Two reverse stages per launch (tile 0: 64x8, 1: 32x16; kz 0: chosen per launch). Arrays of
 // 4 GiB or more are refused (hipErrorInvalidValue): the caller runs single stages then.
 template <typename T>

@@ -29,29 +29,10 @@
 // sweeps and the per-stage kernel read there.
 #include <type_traits>
 
-#include "pf_cell.h"
+#include "pf_brick.h"
 #include "pf_internal.h"
 
 namespace pf {
-
-// e / D for 0 <= e < 2^13 and a constant D: a 24-bit product and a shift, which run at the full
-// rate (the general sequence takes a quarter-rate 32-bit product). With M = floor(2^19 / D) + 1
-// the error e (M D - 2^19) / 2^19 stays below 1 for e < 2^13 and D <= 64, and the product below
-// 2^32 (checked over the whole range by a static assertion at each use).
-template <int D>
-struct SmallDiv {
-    static constexpr unsigned M = (1u << 19) / D + 1u;
-    static constexpr bool exact(unsigned e, unsigned n)
-    {
-        for (; e < n; ++e)
-            if (((e * M) >> 19) != e / D) return false;
-        return true;
-    }
-    static __device__ __forceinline__ int div(int e)
-    {
-        return (int)(__umul24((unsigned)e, M) >> 19);
-    }
-};
 
 template <typename T, int BX, int BY, int BZ>
 struct BrickLayout {
@@ -105,8 +86,8 @@ __global__ void __launch_bounds__(NT) brick_kernel(FusedArgs<T> a, int tiles_x, 
     const bool wx = WALLS && (a.walls & 1), wy = WALLS && (a.walls & 2), wz = WALLS && (a.walls & 4);
     // an index of the brick lies at most 4 cells below the domain and B + 3 cells beyond its end:
     // within one period, or one mirror image, of an axis of B + 4 cells or more (FAST)
-    auto per = [](int v, int n) { return FAST ? wrap1(v, n) : wrapn(v, n); };
-    auto mir = [](int v, int n) { return FAST ? (v < 0 ? -1 - v : (v >= n ? 2 * n - 1 - v : v)) : reflectn(v, n); };
+    auto per = [](int v, int n) { return brick_wrap<FAST>(v, n); };
+    auto mir = [](int v, int n) { return brick_mirror<FAST>(v, n); };
     auto mapx = [&](int v) { return WALLS && wx ? mir(v, nx) : per(v, nx); };
     auto mapy = [&](int v) { return WALLS && wy ? mir(v, ny) : per(v, ny); };
     auto mapz = [&](int v) { return WALLS && wz ? mir(v, nz) : per(v, nz); };

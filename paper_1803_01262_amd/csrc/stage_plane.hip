@@ -19,7 +19,7 @@
 // WALLS: the patch's field is read through mirror indices; the thread of a ghost cell evaluates f at
 // the ghost's mirror partner in the patch, so the ghost holds its partner's value in every stage,
 // which is what the stage launches read there.
-#include "pf_cell.h"
+#include "pf_brick.h"
 #include "pf_internal.h"
 
 namespace pf {
@@ -39,8 +39,8 @@ __global__ void __launch_bounds__(1024) plane_step_kernel(PlaneStepArgs<T> a, in
     const bool wx = WALLS && (a.walls & 1), wy = WALLS && (a.walls & 2), wz = WALLS && (a.walls & 4);
     // the patch reaches at most H + B cells beyond the plane's end: within one period, or one
     // mirror image, of an axis of P cells or more (FAST)
-    auto per = [](int v, int n) { return FAST ? wrap1(v, n) : wrapn(v, n); };
-    auto mir = [](int v, int n) { return FAST ? (v < 0 ? -1 - v : (v >= n ? 2 * n - 1 - v : v)) : reflectn(v, n); };
+    auto per = [](int v, int n) { return brick_wrap<FAST>(v, n); };
+    auto mir = [](int v, int n) { return brick_mirror<FAST>(v, n); };
     const int vx = wx ? mir(ux, nx) : ux, vy = wy ? mir(uy, ny) : uy;
     // where f is evaluated: the cell, or a ghost's partner (in the patch wherever it is needed)
     const int ex = vx - (bi * B - H), ey = vy - (bj * B - H);

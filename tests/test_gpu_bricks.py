@@ -1,4 +1,4 @@
-"""Brick and whole-step forms of small grids (stage_brick.hip, stage_plane.hip): bit-identical to
+"""Brick and whole-step forms of small grids (stage_brick.hip, stage_plane.hip, adjoint_brick.hip): bit-identical to
 the one-thread-per-cell kernel at the edges of their bricks, patches and halos, on every
 boundary, and in every place a handle with the automatic variant takes them."""
 import numpy as np
@@ -72,10 +72,10 @@ def test_plane_step_matches_the_plain_kernel(pf, dtype, walls):
 
 @pytest.mark.parametrize("dtype", ["f32", "f64"])
 @pytest.mark.parametrize("walls", WALLS[:2])
-@pytest.mark.parametrize("shape", [(20, 12, 9), (24, 18, 1)])
+@pytest.mark.parametrize("shape", [(20, 12, 9), (16, 8, 4), (3, 2, 5), (24, 18, 1), (401, 363, 1)])
 def test_stages_and_adjoint_take_bricks(pf, dtype, shape, walls):
-    """step_stages (in and out of place) and the adjoint's recompute of a handle whose steps run in
-    bricks: the bits of the plain kernels."""
+    """step_stages (in and out of place), the adjoint's recompute and its reverse stages on a
+    handle whose steps run in bricks: the bits of the plain kernels."""
     dx = 1.0 / max(shape)
     nm = names(pf, dtype)
     res = []
