@@ -206,16 +206,27 @@ int pf::default_variant(const pf_params& p)
     return wall_mask(p) != 0 ? walled_default_variant(p.dtype, p.n) : tuned_variant(p.dtype, p.n);
 }
 
+// Whether the caller (variant >= 0) or, on a periodic grid, the tuning cache names the variant.
+static bool variant_named(const pf_params& p)
+{
+    if (p.variant >= 0) return true;
+    if (wall_mask(p) != 0) return false;
+    std::lock_guard<std::mutex> lk(g_tune_mu);
+    load_tune_cache_locked();
+    return g_tuned.count(std::make_tuple(p.dtype, p.n[0], p.n[1], p.n[2])) != 0;
+}
+
 int pf::step_variant(const pf_params& p, int variant)
 {
-    if (p.variant >= 0) return variant;
-    const int wm = wall_mask(p);
-    if (wm == 0) {
-        std::lock_guard<std::mutex> lk(g_tune_mu);
-        load_tune_cache_locked();
-        if (g_tuned.count(std::make_tuple(p.dtype, p.n[0], p.n[1], p.n[2]))) return variant;
-    }
-    const int v = small_step_variant(p.n[0], p.n[1], p.n[2], p.dtype, p.scheme, wm != 0);
+    if (variant_named(p)) return variant;
+    const int v = small_step_variant(p.n[0], p.n[1], p.n[2], p.dtype, p.scheme, wall_mask(p) != 0);
+    return v >= 0 ? v : variant;
+}
+
+int pf::single_stage_variant(const pf_params& p, int variant)
+{
+    if (variant_named(p)) return variant;
+    const int v = stage_brick_variant(p.n[0], p.n[1], p.n[2], p.dtype);
     return v >= 0 ? v : variant;
 }
 
@@ -266,6 +277,7 @@ extern "C" pf_status phasefield_create(const pf_params* p, pf_solver** out)
     s->esz = p->dtype == PF_F32 ? sizeof(float) : sizeof(double);
     s->variant = p->variant >= 0 ? p->variant : default_variant(*p);
     s->step_variant = step_variant(*p, s->variant);
+    s->stage_variant = single_stage_variant(*p, s->variant);
     hipError_t e = hipSuccess;
     for (void** b : {&s->ya, &s->yb, &s->acc}) {
         e = hipMalloc(b, s->N * s->esz);
@@ -447,7 +459,7 @@ template <typename T>
 hipError_t pf::run_stage(int variant, const StageArgs<T>& a, hipStream_t st)
 {
     constexpr int dtype = sizeof(T) == 4 ? PF_F32 : PF_F64;
-    if (a.nu[0]) return launch_stage_nu<T>(a, st);
+    if (a.nu[0]) return launch_stage_nu<T>(a, stage_variant(dtype, variant).brick, st);
     const int v = variant_is_fused(dtype, variant) ? per_stage_variant(a.nx, a.ny, a.nz, dtype) : variant;
     const StageVariant& sv = stage_variant(dtype, v);
     if constexpr (sizeof(T) == 4)
@@ -843,7 +855,7 @@ static hipError_t step_stages_impl(pf_solver* s, const T* phi, T* phi_next, cons
     const pf_params& p = s->p;
     const double dt = p.dt;
     T* acc = (T*)s->acc;
-    const int v = s->variant;
+    const int v = s->stage_variant;
     const double sh = time_factor(p, t + 0.5 * dt);
     const NuMesh* nu = s->nu.on() ? &s->nu : nullptr;
     hipError_t e;
@@ -1045,7 +1057,7 @@ static pf_status autotune_impl(pf_solver* s, int reps, int32_t* best, double* ti
     for (T* b : {phi, U, V, W})
         if (b) (void)hipFree(b);
     if (ret == PF_OK) {
-        s->variant = s->step_variant = best_v;
+        s->variant = s->step_variant = s->stage_variant = best_v;
         if (wall_mask(p) == 0) store_tuned(p.dtype, p.n, best_v);  // the cache is for periodic grids
         release_graph(s->graph);
         if (best) *best = best_v;

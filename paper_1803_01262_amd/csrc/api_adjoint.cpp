@@ -165,10 +165,10 @@ static pf_status adjoint_impl(pf_solver* s, const T* phi, const T* U, const T* V
             y3 = stages[1];
             e = hipSuccess;
         } else {
-            e = run_stage<T>(s->variant, make_stage<T>(p, s1, phi, phi, phi, (T*)y2, A, dt * g1,
+            e = run_stage<T>(s->stage_variant, make_stage<T>(p, s1, phi, phi, phi, (T*)y2, A, dt * g1,
                                                        dt * (g1 + z2), U, V, W, nu), st);
             if (e == hipSuccess)
-                e = run_stage<T>(s->variant, make_stage<T>(p, s2, y2, A, nullptr, (T*)y3, nullptr,
+                e = run_stage<T>(s->stage_variant, make_stage<T>(p, s2, y2, A, nullptr, (T*)y3, nullptr,
                                                            dt * g2, 0.0, U, V, W, nu), st);
         }
         if (e == hipSuccess)
@@ -189,7 +189,7 @@ static pf_status adjoint_impl(pf_solver* s, const T* phi, const T* U, const T* V
         const T* y2 = stages ? stages[0] : (T*)s->ya;
         const double s1 = time_factor(p, t), s2 = time_factor(p, t + 0.5 * dt);
         e = stages ? hipSuccess
-                   : run_stage<T>(s->variant, make_stage<T>(p, s1, phi, phi, nullptr, (T*)y2, nullptr,
+                   : run_stage<T>(s->stage_variant, make_stage<T>(p, s1, phi, phi, nullptr, (T*)y2, nullptr,
                                                             0.5 * dt, 0.0, U, V, W, nu), st);
         if (e == hipSuccess)
             e = adj(make_adj<T>(p, s2, y2, lam, dt, lam, L, lam, Ka, 0.0, 0.5 * dt, gU, gV, gW, U,
@@ -211,9 +211,12 @@ static pf_status adjoint_impl(pf_solver* s, const T* phi, const T* U, const T* V
     // 128^3 0.259 / 0.259 ms, 256^3 1.90 / 1.95, 512^3 14.98 / 15.38); on walled grids three
     // per-stage launches.
     const int sv = s->step_variant;
-    const bool brick_rc = stage_variant(p.dtype, sv).brick && p.n[2] > 1;  // bricks take walls
-    const bool fused_rc = !nu && (brick_rc || (variant_is_fused(p.dtype, v) && wall_mask(p) == 0));
-    const int vs = variant_is_fused(p.dtype, v) && !fused_rc ? stage_variant_index(p.dtype, "tiled_64x8") : v;
+    // (two-stage bricks take walls; a grid whose steps run single stages recomputes with them)
+    const bool fused_rc = !nu && variant_is_fused(p.dtype, sv) &&
+                          (stage_variant(p.dtype, sv).brick ? p.n[2] > 1 : wall_mask(p) == 0);
+    const int vs = s->stage_variant != v || fused_rc || !variant_is_fused(p.dtype, v)
+                       ? s->stage_variant
+                       : stage_variant_index(p.dtype, "tiled_64x8");
     if (stages) {
         y2 = (T*)stages[0];
         y3 = (T*)stages[1];
@@ -223,7 +226,7 @@ static pf_status adjoint_impl(pf_solver* s, const T* phi, const T* U, const T* V
         FusedArgs<T> a = make_fused<T>(p, false, t, phi, y4, U, V, W, y3);
         a.out_mid = y2;
         a.out_acc = nullptr;
-        e = run_fused_sweep<T>(brick_rc ? sv : v, a, false, st);
+        e = run_fused_sweep<T>(sv, a, false, st);
     } else {
         e = run_stage<T>(vs, make_stage<T>(p, s1, phi, phi, nullptr, y2, nullptr, 0.5 * dt, 0.0, U, V, W, nu), st);
         if (e == hipSuccess)

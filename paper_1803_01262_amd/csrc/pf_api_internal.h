@@ -50,9 +50,10 @@ pf_status check_field_ptr(const void* ptr, const char* name);
 int scheme_stage_count(int scheme);  // stage inputs an RK step keeps for its adjoint
 int tuned_variant(int dtype, const int32_t n[3]);
 int default_variant(const pf_params& p);  // variant -1: walled grids by rule, else tuned_variant
-// The variant that whole steps of a handle or call of `variant` run: that variant where the caller or
-// the tuning cache named it, else a brick on small grids.
+// The variants that whole steps and single stages of a handle or call of `variant` run: that
+// variant where the caller or the tuning cache named it, else bricks on small grids.
 int step_variant(const pf_params& p, int variant);
+int single_stage_variant(const pf_params& p, int variant);
 void release_graph(StepGraph& g);
 double time_factor(const pf_params& p, double t);
 
@@ -91,8 +92,9 @@ struct pf_solver {
     pf_params p{};
     size_t N = 0;       // cells
     size_t esz = 0;     // bytes per element
-    int variant = 0;       // single stages, the adjoint's tile
-    int step_variant = 0;  // whole steps (step_variant(): a brick on small grids)
+    int variant = 0;        // the reported variant; the adjoint's tile
+    int step_variant = 0;   // whole steps (step_variant(): bricks on small grids)
+    int stage_variant = 0;  // single stages (single_stage_variant())
     int adjoint_form = -1;  // reverse RK4 stages: -1 chosen per grid, 0 one per launch, 1 two
     void* ya = nullptr;  // RK stage buffers
     void* yb = nullptr;

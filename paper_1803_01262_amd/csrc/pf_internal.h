@@ -206,6 +206,13 @@ template <typename T, int TX, int TY, int KZ, bool FORCE_BIG>
 hipError_t launch_fused(const FusedArgs<T>& a, bool sweep_b, hipStream_t st);
 template <typename T, int BX, int BY, int BZ, int NT>
 hipError_t launch_brick(const FusedArgs<T>& a, bool sweep_b, hipStream_t st);
+// The launchers of one stage: the tiled march (stage_tiled.hip) and the bricks (stage_brick1.hip).
+template <typename T, int TX, int TY, int KZ, bool FORCE_BIG, bool NU = false>
+hipError_t launch_stage_tiled(const StageArgs<T>& a, hipStream_t st);
+template <typename T, int BX, int BY, int BZ>
+hipError_t launch_stage_brick(const StageArgs<T>& a, hipStream_t st);
+template <typename T>
+hipError_t launch_stage_nu_march(const StageArgs<T>& a, hipStream_t st);
 
 // ------------------------------------------------------------------ stage-kernel variants
 // Either a per-stage kernel (four launches per RK4 step) or a fused pair of sweeps (two
@@ -216,7 +223,7 @@ struct StageVariant {
     hipError_t (*launch_f64)(const StageArgs<double>&, hipStream_t);
     hipError_t (*fused_f32)(const FusedArgs<float>&, bool sweep_b, hipStream_t);  // fused
     hipError_t (*fused_f64)(const FusedArgs<double>&, bool sweep_b, hipStream_t);
-    bool brick = false;  // the fused form is a brick (stage_brick.hip), not a march
+    bool brick = false;  // runs on bricks (stage_brick.hip, stage_brick1.hip), not in a march
     bool plane = false;  // on one-plane grids, a whole step per launch (stage_plane.hip)
 };
 // Variants available for a storage dtype, indexed 0..count-1 (per dtype).
@@ -227,6 +234,10 @@ bool variant_is_fused(int dtype, int v);
 template <typename T>
 hipError_t launch_plane_step(const PlaneStepArgs<T>& a, int stages, hipStream_t st);
 int default_stage_variant(int nx, int ny, int nz, int dtype);
+// Whether single stages of a grid run on bricks (handles whose variant was not named), and the
+// brick variant for them (-1: the handle's own).
+bool stage_takes_bricks(int nx, int ny, int nz, int dtype, bool nu);
+int stage_brick_variant(int nx, int ny, int nz, int dtype);
 // The brick variant for whole steps of a small grid, or -1: its stage variant's own step.
 int small_step_variant(int nx, int ny, int nz, int dtype, int scheme, bool walls);
 // The per-stage variant that single stages of a fused solver run on (adjoint recompute, Euler).
@@ -318,9 +329,9 @@ int device_compute_units();  // of the current device; 0 on error (cached per de
 template <typename T>
 hipError_t launch_copy(T* dst, const T* src, size_t n, hipStream_t st);
 
-// One stage on a non-uniform mesh (a.nu set): stage_tiled.hip.
+// One stage on a non-uniform mesh (a.nu set): stage_tiled.hip. bricks: the variant is a brick one.
 template <typename T>
-hipError_t launch_stage_nu(const StageArgs<T>& a, hipStream_t st);
+hipError_t launch_stage_nu(const StageArgs<T>& a, bool bricks, hipStream_t st);
 template <typename T>
 hipError_t launch_fill(T* dst, T value, size_t n, hipStream_t st);
 

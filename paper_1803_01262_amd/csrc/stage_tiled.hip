@@ -130,7 +130,7 @@ __global__ void __launch_bounds__(TX* TY) stage_plane_kernel(StageArgs<T> a, int
 // FORCE_BIG selects the per-plane descriptor form even for small arrays (it is what arrays of
 // 4 GiB or more take), so that form can be checked against the default one at any size.
 // NU: the non-uniform mesh form (a.nu set), which marches one-plane grids too.
-template <typename T, int TX, int TY, int KZ, bool FORCE_BIG, bool NU = false>
+template <typename T, int TX, int TY, int KZ, bool FORCE_BIG, bool NU>
 hipError_t launch_stage_tiled(const StageArgs<T>& a, hipStream_t st)
 {
     const int tiles_x = (a.nx + TX - 1) / TX;
@@ -233,6 +233,8 @@ static const StageVariant kVariants[] = {
     PF_BRICK("fused_brick8x8x8", 8, 8, 8, 1024),
     PF_BRICK("fused_brick8x8x4", 8, 8, 4, 512),
     {"fused_brick16x8x8", nullptr, nullptr, launch_brick<float, 16, 8, 8, 1024>, nullptr, true},
+    {"tiled_brick16x8x4", launch_stage_brick<float, 16, 8, 4>, launch_stage_brick<double, 16, 8, 4>,
+     nullptr, nullptr, true},
     // one-plane grids: a whole step per launch (thicker grids run the small bricks)
     {"fused_plane", nullptr, nullptr, launch_brick<float, 8, 8, 4, 512>,
      launch_brick<double, 8, 8, 4, 512>, true, true},
@@ -296,15 +298,25 @@ static bool prefer_x64(int nx)
 }
 
 // A stage on a non-uniform mesh: the tiled per-stage kernel in its NU form on 64x4 tiles (32x4
-// where 64-wide tiles pad more columns), chunk length chosen per launch.
+// where 64-wide tiles pad more columns), chunk length chosen per launch; or, for a brick variant on
+// a small grid, bricks.
 template <typename T>
-hipError_t launch_stage_nu(const StageArgs<T>& a, hipStream_t st)
+hipError_t launch_stage_nu_march(const StageArgs<T>& a, hipStream_t st)
 {
     return prefer_x64(a.nx) ? launch_stage_tiled<T, 64, 4, 0, false, true>(a, st)
                             : launch_stage_tiled<T, 32, 4, 0, false, true>(a, st);
 }
-template hipError_t launch_stage_nu<float>(const StageArgs<float>&, hipStream_t);
-template hipError_t launch_stage_nu<double>(const StageArgs<double>&, hipStream_t);
+template hipError_t launch_stage_nu_march<float>(const StageArgs<float>&, hipStream_t);
+template hipError_t launch_stage_nu_march<double>(const StageArgs<double>&, hipStream_t);
+template <typename T>
+hipError_t launch_stage_nu(const StageArgs<T>& a, bool bricks, hipStream_t st)
+{
+    return bricks && stage_takes_bricks(a.nx, a.ny, a.nz, sizeof(T) == 4 ? PF_F32 : PF_F64, true)
+               ? launch_stage_brick<T, 16, 8, 4>(a, st)
+               : launch_stage_nu_march<T>(a, st);
+}
+template hipError_t launch_stage_nu<float>(const StageArgs<float>&, bool, hipStream_t);
+template hipError_t launch_stage_nu<double>(const StageArgs<double>&, bool, hipStream_t);
 
 // Grids from this many cells up take the fused sweeps by default, smaller ones the per-stage
 // kernels (MI355X, ms per step, best per-stage / best fused: FP32 80^3 0.036 / 0.044, 96^3
@@ -342,32 +354,51 @@ int default_stage_variant(int nx, int ny, int nz, int dtype)
                                       : per_stage_variant(nx, ny, nz, dtype);
 }
 
+// Single stages of small grids run on bricks (stage_brick1.hip): up to 128^3 cells on a uniform
+// mesh, where the march's tiles and chunks catch up with them (MI355X, us per RK3 step, march /
+// bricks: FP32 32^3 20.6 / 10.4, 64^3 21.8 / 13.2, 96^3 29.6 / 25.9, 128^3 49.8 / 49.1, 160^3 68 /
+// 88; FP64 32^3 21.7 / 11.6, 64^3 26.0 / 15.4, 96^3 35.6 / 32.1, 128^3 64.0 / 63.2, 160^3 102 /
+// 121; walls on x and z FP64 80^3 36.7 / 24.5, 128^3 71.5 / 68.2), and less on a non-uniform one,
+// whose tables every brick reads again (RK4: FP32 64^3 33.1 / 21.4, 112^3 75.8 / 66.5, 128^3 85 /
+// 91; FP64 64^3 38.3 / 27.4, 96^3 81 / 74, 112^3 101 / 109). One-plane grids have their own kernel.
+bool stage_takes_bricks(int nx, int ny, int nz, int dtype, bool nu)
+{
+    const long long n = !nu ? 128 : dtype == PF_F32 ? 118 : 102;
+    return nz > 1 && (long long)nx * ny * nz <= n * n * n;
+}
+
+int stage_brick_variant(int nx, int ny, int nz, int dtype)
+{
+    return stage_takes_bricks(nx, ny, nz, dtype, false) ? variant_by_name(dtype, "tiled_brick16x8x4") : -1;
+}
+
 // Whole RK4 and RK2 steps of small grids (and RK3 of one-plane grids): a brick variant, or -1 where
-// the grid's stage variant serves them. One brick per compute unit takes one latency however few
-// cells it has, so the smallest brick that needs at most one per unit wins (MI355X, us per RK4
-// step, per-stage launches / 8x8x4 / 8x8x8 / 16x8x8 bricks: FP32 32^3 27.7 / 11.0 / 13.0 / 14.7,
-// 48^3 28.7 / 14.5 / 13.3 / 15.7, 64^3 29.4 / 23.7 / 20.3 / 16.7, 80^3 35.1 / 33.3 / 30.0 / 25.1,
-// 96^3 40.0 / 53 / 48 / 39.1; FP64 32^3 29.7 / 13.5 / 16.1, 48^3 33.8 / 20.4 / 17.7, 56^3 34.6 /
-// 28.5 / 31.7, 64^3 35.0 / 34.6 / 32.3, 80^3 42 / 59 / 60). From there up the halos that every
-// brick evaluates again cost more than the launches they save; element-wise loads (walls, odd
-// rows) reach that point earlier (FP32 16x8x8 bricks, walls on x and z: 64^3 20.5 against 33.2,
-// 80^3 36.9 against 39.6, 96^3 70 against 45).
+// the grid's stage variant serves them. Two stages per brick while one brick per compute unit (or
+// two, FP32) covers the grid: a launch then takes one latency however few cells it has. From there
+// the halos that every such brick evaluates again cost more than the launches they save, and
+// single-stage bricks lead until the fused marches overtake them (MI355X, us per RK4 step, marches
+// / 8x8x4 / 8x8x8 / 16x8x8 bricks / single stages on 16x8x4: FP32 32^3 27.7 / 11.0 / 13.0 / 14.7 /
+// 13.6, 48^3 28.7 / 14.5 / 13.3 / 15.7 / 14.3, 64^3 29.4 / 23.7 / 20.3 / 16.7 / 17.5, 80^3 35.1 /
+// 33.3 / 30.0 / 25.1 / 24.5, 96^3 40.0 / 53 / 48 / 39.1 / 34.9, 112^3 56.6 / - / - / - / 49.2, 128^3
+// 57.1 / - / - / - / 66.2; FP64 32^3 29.7 / 13.5 / 16.1 / - / 15.4, 48^3 33.8 / 20.4 / 17.7 / - /
+// 16.4, 64^3 35.0 / 34.6 / 32.3 / - / 20.8, 96^3 50.6 / - / - / - / 44.8, 128^3 95.5 / - / - / - /
+// 89.3, 160^3 152 / - / - / - / 170). Element-wise loads (walls) reach that point earlier (FP32,
+// walls on x and z: 48^3 8x8x8 15.0, single stages 15.7; 64^3 16x8x8 20.5, single stages 19.3).
 int small_step_variant(int nx, int ny, int nz, int dtype, int scheme, bool walls)
 {
-    if (scheme == PF_EULER) return -1;
-    if (nz == 1) return variant_by_name(dtype, "fused_plane");
-    if (scheme == PF_RK3) return -1;
+    if (nz == 1) return scheme == PF_EULER ? -1 : variant_by_name(dtype, "fused_plane");
+    const int stage = stage_brick_variant(nx, ny, nz, dtype);
+    if (scheme == PF_EULER || scheme == PF_RK3) return stage;
     auto bricks = [&](int bx, int by, int bz) {
         return (long long)((nx + bx - 1) / bx) * ((ny + by - 1) / by) * ((nz + bz - 1) / bz);
     };
     if (bricks(8, 8, 4) <= 256) return variant_by_name(dtype, "fused_brick8x8x4");
-    if (bricks(8, 8, 8) <= 256) return variant_by_name(dtype, "fused_brick8x8x8");
     if (dtype == PF_F32) {
-        const bool pieces = !walls && nx % 4 == 0;
-        return bricks(16, 8, 8) <= (pieces ? 768 : 512) ? variant_by_name(dtype, "fused_brick16x8x8") : -1;
+        if (bricks(8, 8, 8) <= 256) return variant_by_name(dtype, "fused_brick8x8x8");
+        if (!walls && nx % 4 == 0 && bricks(16, 8, 8) <= 320) return variant_by_name(dtype, "fused_brick16x8x8");
+        if (!walls && (long long)nx * ny * nz > 118LL * 118 * 118) return -1;
     }
-    if (bricks(8, 8, 4) <= 768) return variant_by_name(dtype, "fused_brick8x8x4");
-    return bricks(8, 8, 8) <= 512 ? variant_by_name(dtype, "fused_brick8x8x8") : -1;
+    return stage;
 }
 
 // FP32 on 64x4 tiles unless those pad more columns than 32x4 (512^3: 3.36 ms per RK4 step against

@@ -1,4 +1,4 @@
-"""Brick and whole-step forms of small grids (stage_brick.hip, stage_plane.hip, adjoint_brick.hip): bit-identical to
+"""Brick and whole-step forms of small grids (stage_brick.hip, stage_brick1.hip, stage_plane.hip, adjoint_brick.hip): bit-identical to
 the one-thread-per-cell kernel at the edges of their bricks, patches and halos, on every
 boundary, and in every place a handle with the automatic variant takes them."""
 import numpy as np
@@ -50,7 +50,7 @@ def stepped(pf, shape, dtype, variant, nsteps, **kw):
 def test_bricks_match_the_plain_kernel(pf, dtype, walls):
     nm = names(pf, dtype)
     for shape in SHAPES:
-        for scheme, nsteps in (("rk4", 3), ("rk2", 2)):
+        for scheme, nsteps in (("rk4", 3), ("rk3", 1), ("rk2", 2), ("euler", 2)):
             kw = dict(scheme=scheme, walls=walls, vel_mode=1, vel_T=0.7)
             ref = stepped(pf, shape, dtype, nm.index("global"), nsteps, **kw)
             for v in [k for k in nm if "brick" in k] + [None]:
@@ -96,6 +96,29 @@ def test_stages_and_adjoint_take_bricks(pf, dtype, shape, walls):
     # the plain adjoint sums as the tiled one does: all bits equal
     for k, (a, b) in enumerate(zip(*res)):
         assert torch.equal(a, b), k
+
+
+@pytest.mark.parametrize("eps_mode", [0, 1])
+@pytest.mark.parametrize("dtype", ["f32", "f64"])
+@pytest.mark.parametrize("walls", WALLS[:3])
+def test_stretched_bricks_match_the_march(pf, dtype, walls, eps_mode):
+    """A non-uniform mesh: the automatic variant's bricks against a named variant's march."""
+    nm = names(pf, dtype)
+    for shape in [(16, 8, 4), (19, 13, 9), (3, 2, 5), (33, 9, 8)]:
+        rng = np.random.default_rng(5)
+        dx = 1.0 / max(shape)
+        h = [dx * rng.uniform(0.7, 1.4, n) for n in shape]
+        res = []
+        for variant in (nm.index("tiled_32x4"), -1):
+            g = fields(shape, dtype)
+            s = pf.Solver(shape, dx, dx, 1.0, 0.03 * dx, dtype=dtype, variant=variant, walls=walls)
+            s.set_spacing(*[list(a) for a in h], eps_mode=eps_mode)
+            print("case", shape, dtype, walls, eps_mode, variant, flush=True)
+            s.step(*g, nsteps=2)
+            torch.cuda.synchronize()
+            s.close()
+            res.append(g[0])
+        assert torch.equal(*res), shape
 
 
 def test_bricks_replay_from_graphs(pf):
