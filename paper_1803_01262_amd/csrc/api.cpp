@@ -219,7 +219,7 @@ static bool variant_named(const pf_params& p)
 int pf::step_variant(const pf_params& p, int variant)
 {
     if (variant_named(p)) return variant;
-    const int v = small_step_variant(p.n[0], p.n[1], p.n[2], p.dtype, p.scheme, wall_mask(p) != 0);
+    const int v = auto_step_variant(p.n[0], p.n[1], p.n[2], p.dtype, p.scheme, wall_mask(p) != 0);
     return v >= 0 ? v : variant;
 }
 

@@ -12,7 +12,8 @@ namespace pf {
 // FP64 needs more registers than that and runs at two waves per SIMD.
 // XOUT: the optional outputs (out_mid; sweep A also out_phi). WALLS: x and/or y walled (a.walls),
 // element-wise plane loads, single-descriptor addressing.
-template <typename T, int TX, int TY, bool SWEEP_B, bool BIG, bool WIDE, bool XOUT, bool WALLS = false>
+template <typename T, int TX, int TY, bool SWEEP_B, bool BIG, bool WIDE, bool XOUT, bool WALLS = false,
+          bool EXITS = false>
 __global__ void __launch_bounds__(TX* TY) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 4 : 2)))
 fused_kernel(FusedArgs<T> a, int tiles_x, int tiles_y, int kz)
 {
@@ -21,30 +22,30 @@ fused_kernel(FusedArgs<T> a, int tiles_x, int tiles_y, int kz)
     b /= tiles_x;
     const int tj = b % tiles_y;
     const int k0 = (b / tiles_y) * kz;
-    fused_body<T, TX, TY, SWEEP_B, BIG, WIDE, XOUT, WALLS, fused_lag<T, TX, TY>()>(a, ti, tj, k0,
-                                                                            min(k0 + kz, a.nz));
+    fused_body<T, TX, TY, SWEEP_B, BIG, WIDE, XOUT, WALLS, fused_lag<T, TX, TY>(), EXITS>(
+        a, ti, tj, k0, min(k0 + kz, a.nz));
 }
 
-template <typename T, int TX, int TY, bool BIG, bool WIDE, bool WALLS = false>
+template <typename T, int TX, int TY, bool BIG, bool WIDE, bool WALLS = false, bool EXITS = false>
 hipError_t launch_fused_sweep(const FusedArgs<T>& a, bool sweep_b, unsigned blocks, int tiles_x,
                               int tiles_y, int kz, hipStream_t st)
 {
     if (sweep_b) {
         if constexpr (!WALLS) {  // sweep B with out_mid: periodic x and y only
             if (a.out_mid) {
-                hipLaunchKernelGGL((fused_kernel<T, TX, TY, true, BIG, WIDE, true, false>),
+                hipLaunchKernelGGL((fused_kernel<T, TX, TY, true, BIG, WIDE, true, false, EXITS>),
                                    dim3(blocks), dim3(TX * TY), 0, st, a, tiles_x, tiles_y, kz);
                 return hipGetLastError();
             }
         }
         if (a.out_mid || a.out_phi) return hipErrorInvalidValue;
-        hipLaunchKernelGGL((fused_kernel<T, TX, TY, true, BIG, WIDE, false, WALLS>), dim3(blocks),
+        hipLaunchKernelGGL((fused_kernel<T, TX, TY, true, BIG, WIDE, false, WALLS, EXITS>), dim3(blocks),
                            dim3(TX * TY), 0, st, a, tiles_x, tiles_y, kz);
     } else if (a.out_mid || a.out_phi)
-        hipLaunchKernelGGL((fused_kernel<T, TX, TY, false, BIG, WIDE, true, WALLS>), dim3(blocks),
+        hipLaunchKernelGGL((fused_kernel<T, TX, TY, false, BIG, WIDE, true, WALLS, EXITS>), dim3(blocks),
                            dim3(TX * TY), 0, st, a, tiles_x, tiles_y, kz);
     else
-        hipLaunchKernelGGL((fused_kernel<T, TX, TY, false, BIG, WIDE, false, WALLS>), dim3(blocks),
+        hipLaunchKernelGGL((fused_kernel<T, TX, TY, false, BIG, WIDE, false, WALLS, EXITS>), dim3(blocks),
                            dim3(TX * TY), 0, st, a, tiles_x, tiles_y, kz);
     return hipGetLastError();
 }
@@ -52,48 +53,53 @@ hipError_t launch_fused_sweep(const FusedArgs<T>& a, bool sweep_b, unsigned bloc
 // KZ: planes per z-chunk, a host-side choice (every KZ shares the kernels of its tile shape);
 // KZ = 0 chooses it per launch (launch_chunk_planes) for the grid and the current device.
 // FORCE_BIG selects the per-plane descriptor form even for small arrays (see the tiled launcher).
+template <typename T, int TX, int TY, int KZ, bool BIG, bool WIDE, bool WALLS>
+static hipError_t launch_fused_form(const FusedArgs<T>& a, bool sweep_b, hipStream_t st)
+{
+    const int tiles_x = (a.nx + TX - 1) / TX, tiles_y = (a.ny + TY - 1) / TY;
+    const long long tiles = (long long)tiles_x * tiles_y;
+    int kz = KZ;
+    bool exits = false;
+    if constexpr (KZ == 0) {
+        // chunks below kExitPlanes take the march that leaves its last group at the chunk's end
+        // (us per step, whole groups / exits: FP32 112^3 56.7 / 47.3, 128^3 57.0 / 51.5, 512^3 (one
+        // chunk) 1937 / 1965; FP64 112^3 94.7 / 78.2, 128^3 95.8 / 89.5, 192^3 279 / 265). Sweeps A
+        // and B share the register budget, hence the residency, of their form.
+        constexpr int kExitPlanes = 64;
+        kz = launch_chunk_planes((const void*)fused_kernel<T, TX, TY, false, BIG, WIDE, false, WALLS, true>,
+                                 TX * TY, tiles, a.nz, 5, 1);
+        exits = kz < kExitPlanes;
+        if (!exits)
+            kz = launch_chunk_planes((const void*)fused_kernel<T, TX, TY, false, BIG, WIDE, false, WALLS, false>,
+                                     TX * TY, tiles, a.nz, 5);
+        if (kz <= 0) return hipErrorInvalidDevice;
+    }
+    const long long blocks = tiles * ((a.nz + kz - 1) / kz);
+    if (blocks <= 0 || blocks > 0x7fffffffLL) return hipErrorInvalidValue;
+    if constexpr (KZ == 0)
+        if (exits)
+            return launch_fused_sweep<T, TX, TY, BIG, WIDE, WALLS, true>(a, sweep_b, (unsigned)blocks, tiles_x,
+                                                                         tiles_y, kz, st);
+    return launch_fused_sweep<T, TX, TY, BIG, WIDE, WALLS, false>(a, sweep_b, (unsigned)blocks, tiles_x, tiles_y,
+                                                                  kz, st);
+}
+
 template <typename T, int TX, int TY, int KZ, bool FORCE_BIG>
 hipError_t launch_fused(const FusedArgs<T>& a, bool sweep_b, hipStream_t st)
 {
-    const int tiles_x = (a.nx + TX - 1) / TX;
-    const int tiles_y = (a.ny + TY - 1) / TY;
-    if (a.nz <= 0 || tiles_x <= 0 || tiles_y <= 0) return hipErrorInvalidValue;
+    if (a.nx <= 0 || a.ny <= 0 || a.nz <= 0) return hipErrorInvalidValue;
     // 16-byte plane loads need rows that are a whole number of 16-byte pieces
     const bool wide = a.nx % (16 / (int)sizeof(T)) == 0;
-    const bool big = FORCE_BIG || field_needs_big(a.nx, a.ny, a.nz, sizeof(T));
-    if (a.walls) {
-        // walled axes: one form (mirror reads element by element, single-descriptor addressing:
-        // arrays below 4 GiB, also for the variants that force the large-array form)
-        if (field_needs_big(a.nx, a.ny, a.nz, sizeof(T))) return hipErrorInvalidValue;
-        int kzw = KZ;
-        if (KZ == 0) {
-            const void* k = (const void*)fused_kernel<T, TX, TY, false, false, false, false, true>;
-            kzw = launch_chunk_planes(k, TX * TY, (long long)tiles_x * tiles_y, a.nz, 5);
-            if (kzw <= 0) return hipErrorInvalidDevice;
-        }
-        const long long wb = (long long)tiles_x * tiles_y * ((a.nz + kzw - 1) / kzw);
-        if (wb <= 0 || wb > 0x7fffffffLL) return hipErrorInvalidValue;
-        return launch_fused_sweep<T, TX, TY, false, false, true>(a, sweep_b, (unsigned)wb, tiles_x,
-                                                                 tiles_y, kzw, st);
-    }
-    int kz = KZ;
-    if (KZ == 0) {
-        // sweeps A and B share the register budget, hence the residency, of their form
-        const void* k = big ? (wide ? (const void*)fused_kernel<T, TX, TY, false, true, true, false>
-                                    : (const void*)fused_kernel<T, TX, TY, false, true, false, false>)
-                            : (wide ? (const void*)fused_kernel<T, TX, TY, false, false, true, false>
-                                    : (const void*)fused_kernel<T, TX, TY, false, false, false, false>);
-        kz = launch_chunk_planes(k, TX * TY, (long long)tiles_x * tiles_y, a.nz, 5);
-        if (kz <= 0) return hipErrorInvalidDevice;
-    }
-    const long long blocks = (long long)tiles_x * tiles_y * ((a.nz + kz - 1) / kz);
-    if (blocks <= 0 || blocks > 0x7fffffffLL) return hipErrorInvalidValue;
-    const unsigned nb = (unsigned)blocks;
-    if (big)
-        return wide ? launch_fused_sweep<T, TX, TY, true, true>(a, sweep_b, nb, tiles_x, tiles_y, kz, st)
-                    : launch_fused_sweep<T, TX, TY, true, false>(a, sweep_b, nb, tiles_x, tiles_y, kz, st);
-    return wide ? launch_fused_sweep<T, TX, TY, false, true>(a, sweep_b, nb, tiles_x, tiles_y, kz, st)
-                : launch_fused_sweep<T, TX, TY, false, false>(a, sweep_b, nb, tiles_x, tiles_y, kz, st);
+    const bool needs_big = field_needs_big(a.nx, a.ny, a.nz, sizeof(T));
+    if (a.walls)  // one form (mirror reads element by element, single-descriptor addressing: arrays
+                  // below 4 GiB, also for the variants that force the large-array form)
+        return needs_big ? hipErrorInvalidValue
+                         : launch_fused_form<T, TX, TY, KZ, false, false, true>(a, sweep_b, st);
+    if (FORCE_BIG || needs_big)
+        return wide ? launch_fused_form<T, TX, TY, KZ, true, true, false>(a, sweep_b, st)
+                    : launch_fused_form<T, TX, TY, KZ, true, false, false>(a, sweep_b, st);
+    return wide ? launch_fused_form<T, TX, TY, KZ, false, true, false>(a, sweep_b, st)
+                : launch_fused_form<T, TX, TY, KZ, false, false, false>(a, sweep_b, st);
 }
 
 }  // namespace pf

@@ -166,15 +166,17 @@ inline bool field_needs_big(int nx, int ny, int nz, size_t es)
 
 // ------------------------------------------------------------------ z-chunks of the marches
 // Every tiled kernel (per-stage, fused, adjoint) gives each workgroup a column tile and a chunk of
-// consecutive planes, marched in whole groups of six iterations after a warm-up. The chunk
-// length is a launch-time choice: the number of chunks c minimises
-//   rounds x (6 ceil((kz + 2) / 6) + extra),   kz = ceil(nz / c),
+// consecutive planes, marched after a warm-up. The chunk length is a launch-time choice: the number
+// of chunks c minimises
+//   rounds x (group ceil((kz + 2) / group) + extra),   kz = ceil(nz / c),
 // where a round is one workgroup per resident slot and the second factor is the iterations one
-// workgroup runs (extra: warm-up beyond the two planes every march needs, plus start-up; about 5
-// for the fused sweeps, 1 for the per-stage and adjoint kernels, as measured on MI355X). Longer
-// chunks repeat less warm-up and re-read fewer halo planes; more chunks fill the device. Ties go
-// to the longer chunk.
-inline int march_chunk_planes(long long tiles, int nz, long long slots, int extra)
+// workgroup runs (group: the marches run whole groups of six iterations, except those that leave the
+// last group at the chunk's end, group 1; extra: warm-up beyond the two planes every march needs,
+// plus start-up; about 5 for the fused sweeps, 1 for the others, as measured on MI355X).
+// Longer chunks repeat less warm-up and re-read fewer halo planes; more chunks fill the device. Ties
+// go to the longer chunk.
+inline int march_chunk_planes(long long tiles, int nz, long long slots, int extra, int group,
+                              long long* cost_out = nullptr)
 {
     int best_kz = nz;
     long long best = -1;
@@ -184,12 +186,13 @@ inline int march_chunk_planes(long long tiles, int nz, long long slots, int extr
         const int kz = (nz + c - 1) / c;
         if (c > 1 && kz == (nz + c - 2) / (c - 1)) continue;  // same chunks as c - 1
         const long long rounds = (tiles * ((nz + kz - 1) / kz) + slots - 1) / slots;
-        const long long cost = rounds * (6 * ((kz + 7) / 6) + extra);
+        const long long cost = rounds * (group * ((kz + 1 + group) / group) + extra);
         if (best < 0 || cost < best) {
             best = cost;
             best_kz = kz;
         }
     }
+    if (cost_out) *cost_out = best;
     return best_kz;
 }
 
@@ -198,7 +201,7 @@ inline int march_chunk_planes(long long tiles, int nz, long long slots, int extr
 int resident_groups_per_cu(const void* kernel, int threads);
 // Chunk length for a launch of `kernel` over `tiles` column tiles of an nz-plane grid on the
 // current device (march_chunk_planes with the device's resident slots); 0 on error.
-int launch_chunk_planes(const void* kernel, int threads, long long tiles, int nz, int extra);
+int launch_chunk_planes(const void* kernel, int threads, long long tiles, int nz, int extra, int group = 6);
 
 // The launchers of the fused two-stage sweeps: the z-marches (pf_fused_launch.h) and the bricks
 // (stage_brick.hip).
@@ -238,8 +241,9 @@ int default_stage_variant(int nx, int ny, int nz, int dtype);
 // brick variant for them (-1: the handle's own).
 bool stage_takes_bricks(int nx, int ny, int nz, int dtype, bool nu);
 int stage_brick_variant(int nx, int ny, int nz, int dtype);
-// The brick variant for whole steps of a small grid, or -1: its stage variant's own step.
-int small_step_variant(int nx, int ny, int nz, int dtype, int scheme, bool walls);
+// The variant for whole steps of a grid (bricks on small ones; FP32 marches on the tile that covers
+// the grid and the device in fewer iterations), or -1: its stage variant's own step.
+int auto_step_variant(int nx, int ny, int nz, int dtype, int scheme, bool walls);
 // The per-stage variant that single stages of a fused solver run on (adjoint recompute, Euler).
 int per_stage_variant(int nx, int ny, int nz, int dtype);
 // Index of the variant of that name (0 if there is none).

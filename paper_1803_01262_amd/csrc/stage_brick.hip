@@ -13,7 +13,7 @@
 // each cell on a thread of its own. The halo is evaluated again by every brick that needs it (an
 // 8 x 8 x 8 brick: 5.1 x its cells in q1, 3.4 x in E1), which costs nothing while compute units
 // are idle. What bounds it: latency (launch, one load round, four barriers), then vector issue.
-// 32^3 FP32 RK4 step from graphs: four per-stage launches 27.7 us, two brick launches 11.0 (small_step_variant
+// 32^3 FP32 RK4 step from graphs: four per-stage launches 27.7 us, two brick launches 11.0 (auto_step_variant
 // has the other sizes and the line to the marches).
 //
 // Same arguments, same arithmetic in the same order as the fused sweeps, hence the same bits.

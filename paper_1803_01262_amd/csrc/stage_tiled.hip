@@ -380,11 +380,11 @@ int stage_brick_variant(int nx, int ny, int nz, int dtype)
 // / 8x8x4 / 8x8x8 / 16x8x8 bricks / single stages on 16x8x4: FP32 32^3 27.7 / 11.0 / 13.0 / 14.7 /
 // 13.6, 48^3 28.7 / 14.5 / 13.3 / 15.7 / 14.3, 64^3 29.4 / 23.7 / 20.3 / 16.7 / 17.5, 80^3 35.1 /
 // 33.3 / 30.0 / 25.1 / 24.5, 96^3 40.0 / 53 / 48 / 39.1 / 34.9, 112^3 56.6 / - / - / - / 49.2, 128^3
-// 57.1 / - / - / - / 66.2; FP64 32^3 29.7 / 13.5 / 16.1 / - / 15.4, 48^3 33.8 / 20.4 / 17.7 / - /
+// 57.1 (51.3 now) / - / - / - / 66.2; FP64 32^3 29.7 / 13.5 / 16.1 / - / 15.4, 48^3 33.8 / 20.4 / 17.7 / - /
 // 16.4, 64^3 35.0 / 34.6 / 32.3 / - / 20.8, 96^3 50.6 / - / - / - / 44.8, 128^3 95.5 / - / - / - /
 // 89.3, 160^3 152 / - / - / - / 170). Element-wise loads (walls) reach that point earlier (FP32,
 // walls on x and z: 48^3 8x8x8 15.0, single stages 15.7; 64^3 16x8x8 20.5, single stages 19.3).
-int small_step_variant(int nx, int ny, int nz, int dtype, int scheme, bool walls)
+int auto_step_variant(int nx, int ny, int nz, int dtype, int scheme, bool walls)
 {
     if (nz == 1) return scheme == PF_EULER ? -1 : variant_by_name(dtype, "fused_plane");
     const int stage = stage_brick_variant(nx, ny, nz, dtype);
@@ -393,12 +393,25 @@ int small_step_variant(int nx, int ny, int nz, int dtype, int scheme, bool walls
         return (long long)((nx + bx - 1) / bx) * ((ny + by - 1) / by) * ((nz + bz - 1) / bz);
     };
     if (bricks(8, 8, 4) <= 256) return variant_by_name(dtype, "fused_brick8x8x4");
-    if (dtype == PF_F32) {
-        if (bricks(8, 8, 8) <= 256) return variant_by_name(dtype, "fused_brick8x8x8");
-        if (!walls && nx % 4 == 0 && bricks(16, 8, 8) <= 320) return variant_by_name(dtype, "fused_brick16x8x8");
-        if (!walls && (long long)nx * ny * nz > 118LL * 118 * 118) return -1;
-    }
-    return stage;
+    if (dtype != PF_F32) return stage;
+    if (bricks(8, 8, 8) <= 256) return variant_by_name(dtype, "fused_brick8x8x8");
+    if (!walls && nx % 4 == 0 && bricks(16, 8, 8) <= 320) return variant_by_name(dtype, "fused_brick16x8x8");
+    const long long cells = (long long)nx * ny * nz, n = walls ? 128 : 108;
+    if (cells <= n * n * n || field_needs_big(nx, ny, nz, 4)) return stage;
+    // FP32 marches: the tile whose columns and z-chunks cover the grid in fewer iterations on two
+    // workgroups per compute unit (us per step, 32x16 / 64x8, and their iterations: 250x200x150 157 / 132,
+    // 45 / 37; 160^3 76.9 / 90.9, 23 / 27; 151x173x129 79.6 / 93.9, 22 / 26). On a tie 64x8 from 256^3
+    // cells (275 / 266 us; 512^3 2081 / 1920), 32x16 below and with walls (256^3 354 / 367).
+    const long long slots = 2LL * device_compute_units();
+    if (slots <= 0) return -1;
+    auto iterations = [&](int tx, int ty) {
+        long long c = 0;
+        (void)march_chunk_planes((long long)((nx + tx - 1) / tx) * ((ny + ty - 1) / ty), nz, slots, 5, 1, &c);
+        return c;
+    };
+    const long long c64 = iterations(64, 8), c32 = iterations(32, 16);
+    const bool x64 = c64 < c32 || (c64 == c32 && !walls && cells >= kX64MinCellsF32);
+    return variant_by_name(dtype, x64 ? "fused_64x8" : "fused_32x16");
 }
 
 // FP32 on 64x4 tiles unless those pad more columns than 32x4 (512^3: 3.36 ms per RK4 step against

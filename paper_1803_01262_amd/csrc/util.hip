@@ -80,12 +80,12 @@ int resident_groups_per_cu(const void* kernel, int threads)
     return groups;
 }
 
-int launch_chunk_planes(const void* kernel, int threads, long long tiles, int nz, int extra)
+int launch_chunk_planes(const void* kernel, int threads, long long tiles, int nz, int extra, int group)
 {
     const int cus = device_compute_units();
     const int groups = resident_groups_per_cu(kernel, threads);
     if (cus <= 0 || groups <= 0 || tiles <= 0 || nz <= 0) return 0;
-    return march_chunk_planes(tiles, nz, (long long)cus * groups, extra);
+    return march_chunk_planes(tiles, nz, (long long)cus * groups, extra, group);
 }
 
 static unsigned grid_for(size_t n)
