@@ -36,6 +36,18 @@ __device__ __forceinline__ void for_batch_tiles(const BatchTile* __restrict__ ti
     }
 }
 
+// An instance's arguments in the constant address space (the tables are written before the launch
+// and never during it), so that the march reads them with scalar loads wherever it needs them: read
+// through an ordinary pointer they are held in vector registers across its barriers and stores, and
+// the FP32 sweep B spilled 12 of them (40 instances of 32^3-128^3: BATCHNUM ms per 8 steps).
+template <typename A>
+using ConstArgs = const __attribute__((address_space(4))) A;
+template <typename A>
+__device__ __forceinline__ ConstArgs<A>& const_args(const A* table, int b)
+{
+    return ((ConstArgs<A>*)table)[__builtin_amdgcn_readfirstlane(b)];
+}
+
 template <typename T, bool PERSIST, bool WALLS>
 __global__ void __launch_bounds__(kBTX* kBTY) batch_stage_kernel(const StageArgs<T>* __restrict__ args,
                                                                   const BatchTile* __restrict__ tiles,
@@ -59,9 +71,11 @@ __global__ void __launch_bounds__(TX* TY) __attribute__((amdgpu_waves_per_eu(siz
 batch_fused_kernel(const FusedArgs<T>* __restrict__ args, const BatchTile* __restrict__ tiles, int len)
 {
     for_batch_tiles<PERSIST>(tiles, len, [&](const BatchTile& tl) {
-        const int k0 = tl.tk * kFKZ;
+        const int k0 = __builtin_amdgcn_readfirstlane(tl.tk) * kFKZ;
+        auto& a = const_args(args, tl.b);
         fused_body<T, TX, TY, SWEEP_B, false, WIDE, false, WALLS, fused_lag<T, TX, TY>()>(
-            args[tl.b], tl.ti, tl.tj, k0, min(k0 + kFKZ, args[tl.b].nz));
+            a, __builtin_amdgcn_readfirstlane(tl.ti), __builtin_amdgcn_readfirstlane(tl.tj), k0,
+            min(k0 + kFKZ, a.nz));
     });
 }
 

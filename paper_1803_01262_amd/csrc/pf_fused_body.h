@@ -32,18 +32,20 @@
 //   Q2X  x-sharpening of E2, 2 planes        [i0-1, i0+TX+1) x [j0, j0+TY)
 //   Q2Y  y-sharpening of E2, 2 planes        [i0, i0+TX) x [j0-1, j0+TY+1)
 //   PB   phi on MID (sweep B only), 1 plane
-//   VEL  FP64 only: U, V of plane t+2 and W of plane t+3 on the MID rows (V with one more
-//        row), loaded one plane ahead in 16-byte pieces where rows allow. FP32 reads the
+//   VEL  FP64 only: U, V and W of plane t+3 on the MID rows (V with one more row), loaded one plane ahead in 16-byte pieces where rows allow. FP32 reads the
 //        velocities at the E1 cells directly: within its 128-register budget the staging
 //        registers spill, and staging ran slower (also with U and V alone).
 // Pipeline: iteration t loads input plane t+4, E1 computes q1 at plane t+3 and ya at plane
 // t+2, E2 computes q2 at plane t+1 and the outputs of plane t. Six warm-up iterations precede
 // the first output plane of a z-chunk: four with E1 alone (a straight-line prologue), then the
-// main loop, which runs E1 and E2 in whole groups of six unconditional iterations so that the
-// values handed from plane to plane stay in place; iterations past the chunk end compute on
-// wrapped planes and store nothing. Two barriers per iteration. EXITS leaves the last group at the
-// chunk's end instead: short chunks save up to five iterations, and long ones lose 1-2 % because
-// the loads of an iteration are no longer moved up into the one before it (launch_fused).
+// main loop, which runs E1 and E2 in groups of six iterations, so that the values handed from plane
+// to plane stay in place, and leaves the last group at the chunk's end. Two barriers per iteration.
+// A plane's neighbours are read from LDS once per evaluation: while the sharpening products of
+// plane p+1 are formed, its own four faces' terms are too, and f of that plane finishes from them in
+// the next iteration; a cell's own values stay in registers. LDS reads per evaluated cell 13 -> 9
+// (E2: 16 -> 8), us per step before / after: FP32 128^3 51.3 / 47.2, 192^3 115.6 / 104.6, 512^3
+// 1920 / 1829; FP64 128^3 89.5 / 82.9, 256^3 511 / 466, 512^3 3940 / 3685 (the exits matter: in whole
+// groups of six the compiler moves loads across iterations, spills, and FP32 512^3 takes 2156).
 // LAG (the one-barrier march): E2 trails E1 by one more plane (q2 at plane t, outputs of plane
 // t-1) and each iteration commits the planes of the next one, so that within an iteration every
 // LDS read is of data written in earlier iterations and every write goes to a slot nobody reads
@@ -86,10 +88,11 @@ constexpr bool fused_lag()
     return sizeof(T) == 8 && TX == 32;
 }
 
-// The workgroup owns the TX x TY column tile (ti, tj) and the output planes [k0, k1).
+// The workgroup owns the TX x TY column tile (ti, tj) and the output planes [k0, k1). Args: FusedArgs<T>,
+// in any address space.
 template <typename T, int TX, int TY, bool SWEEP_B, bool BIG, bool WIDE, bool XOUT = false,
-          bool WALLS = false, bool LAG = false, bool EXITS = false>
-__device__ __forceinline__ void fused_body(const FusedArgs<T>& a, int ti, int tj, int k0, int k1)
+          bool WALLS = false, bool LAG = false, typename Args = const FusedArgs<T>>
+__device__ __forceinline__ void fused_body(Args& a, int ti, int tj, int k0, int k1)
 {
     static_assert(!(WALLS && WIDE), "mirror reads are element-wise");
     constexpr int NT = TX * TY;
@@ -258,41 +261,30 @@ __device__ __forceinline__ void fused_body(const FusedArgs<T>& a, int ti, int tj
         }
     }
 
-    // ---- plane loads: IN (stage input with halo 4) and, for sweep B, phi on MID
+    // ---- plane loads: IN (stage input with halo 4) and, for sweep B, phi on MID. Piece e = tid + s NT
+    // of a plane lands at LDS element e * LV (rows are whole numbers of pieces); only its source
+    // offset is kept per thread
+    constexpr int LV = WIDE ? VEC : 1;
+    constexpr int NPI = INS / LV, NPB = PBS / LV;  // pieces of a plane
+    static_assert(!WIDE || (INW % VEC == 0 && PBW == INW), "whole pieces per row");
     unsigned li_off[NLI];
-    int li_pos[NLI];
 #pragma unroll
     for (int s = 0; s < NLI; ++s) {
-        const int e = tid + s * NT;
-        if (WIDE) {
-            const int r = e / INGW, g = e - r * INGW;
-            li_pos[s] = e < INGW * INH ? r * INW + g * VEC : -1;
-            li_off[s] = e < INGW * INH
-                            ? (unsigned)(wrapn(j0 - 4 + r, ny) * nx + wrapn(i0 - 4 + g * VEC, nx)) * ES
+        const int e = tid + s * NT, r = e / (INW / LV), c = (e - r * (INW / LV)) * LV;
+        li_off[s] = e < NPI ? (unsigned)(WIDE ? wrapn(j0 - 4 + r, ny) * nx + wrapn(i0 - 4 + c, nx)
+                                              : mapy(j0 - 4 + r) * nx + mapx(i0 - 4 + c)) * ES
                             : 0u;
-        } else {
-            const int r = e / INW, c = e - r * INW;
-            li_pos[s] = e < INS ? e : -1;
-            li_off[s] = e < INS ? (unsigned)(mapy(j0 - 4 + r) * nx + mapx(i0 - 4 + c)) * ES : 0u;
-        }
     }
     unsigned lb_off[NLB > 0 ? NLB : 1];
-    int lb_pos[NLB > 0 ? NLB : 1];
 #pragma unroll
     for (int s = 0; s < NLB; ++s) {
-        const int e = tid + s * NT;
-        if (WIDE) {
-            const int r = e / INGW, g = e - r * INGW;
-            lb_pos[s] = e < INGW * MH ? r * PBW + g * VEC : -1;
-            lb_off[s] = e < INGW * MH
-                            ? (unsigned)(wrapn(j0 - 2 + r, ny) * nx + wrapn(i0 - 4 + g * VEC, nx)) * ES
+        const int e = tid + s * NT, r = e / (PBW / LV), c = (e - r * (PBW / LV)) * LV;
+        lb_off[s] = e < NPB ? (unsigned)(WIDE ? wrapn(j0 - 2 + r, ny) * nx + wrapn(i0 - 4 + c, nx)
+                                              : mapy(j0 - 2 + r) * nx + mapx(i0 - 2 + c)) * ES
                             : 0u;
-        } else {
-            const int r = e / MW, c = e - r * MW;
-            lb_pos[s] = e < MS ? e : -1;
-            lb_off[s] = e < MS ? (unsigned)(mapy(j0 - 2 + r) * nx + mapx(i0 - 2 + c)) * ES : 0u;
-        }
     }
+    auto in_on = [&](int s) { return (s + 1) * NT <= NPI || tid + s * NT < NPI; };
+    auto b_on = [&](int s) { return (s + 1) * NT <= NPB || tid + s * NT < NPB; };
     // velocity staging loads: a flattened list of the U, V and W pieces, NLV per thread
     constexpr int PPR = WIDE ? INGW : INW, PV = WIDE ? VEC : 1;  // pieces per row, their width
     constexpr int NGU = PPR * MH, NGV = PPR * (MH + 1), NGVEL = 2 * NGU + NGV;
@@ -332,24 +324,24 @@ __device__ __forceinline__ void fused_body(const FusedArgs<T>& a, int ti, int tj
         const int kw = mapz(kk);
 #pragma unroll
         for (int s = 0; s < NLI; ++s)
-            if (li_pos[s] >= 0) pre_in[s] = load_piece(fy, kw, li_off[s]);
+            if (in_on(s)) pre_in[s] = load_piece(fy, kw, li_off[s]);
     };
     auto commit_in = [&](int slot) {
 #pragma unroll
         for (int s = 0; s < NLI; ++s)
-            if (li_pos[s] >= 0) put_piece(s_in + slot * INS + li_pos[s], pre_in[s]);
+            if (in_on(s)) put_piece(s_in + slot * INS + (tid + s * NT) * LV, pre_in[s]);
     };
     auto fetch_b = [&](int kk) {
         const int kw = mapz(kk);
 #pragma unroll
         for (int s = 0; s < NLB; ++s)
-            if (lb_pos[s] >= 0) pre_b[s] = load_piece(fphi, kw, lb_off[s]);
+            if (b_on(s)) pre_b[s] = load_piece(fphi, kw, lb_off[s]);
     };
     piece_t pre_v[NLV > 0 ? NLV : 1];
-    auto fetch_vel = [&](int p) {  // U, V at plane p, W at plane p+1
+    auto fetch_vel = [&](int p) {  // U, V and W at plane p
         const int kw = mapz(p);
         int kw1;
-        const int sg1 = wface(p + 1, kw1);
+        const int sg1 = wface(p, kw1);
 #pragma unroll
         for (int s = 0; s < NLV; ++s) {
             const int e = tid + s * NT;
@@ -375,17 +367,21 @@ __device__ __forceinline__ void fused_body(const FusedArgs<T>& a, int ti, int tj
     auto commit_b = [&](int slot) {
 #pragma unroll
         for (int s = 0; s < NLB; ++s)
-            if (lb_pos[s] >= 0) put_piece(s_pb + slot * PBS + lb_pos[s], pre_b[s]);
+            if (b_on(s)) put_piece(s_pb + slot * PBS + (tid + s * NT) * LV, pre_b[s]);
     };
 
-    // per-slot z state of E1 (q1_z and the z-face flux) and of E2
     // per-slot z state of E1 at plane p: q1_z at p-1 and p, sum and difference of phi on the
     // face (p-1, p), W at p; the same for E2 at plane t
     T e_qzm[2] = {T(0), T(0)}, e_qz[2] = {T(0), T(0)}, e_sz[2] = {T(0), T(0)};
     T e_dz[2] = {T(0), T(0)}, e_w0[2] = {T(0), T(0)};
     T q2zm = T(0), q2z = T(0), sz2 = T(0), dz2 = T(0), w2 = T(0);
-    // own-cell queues from E1 (plane p) to E2 (plane p, NQ-1 iterations later): after E1 of
-    // iteration t they hold planes t+3-NQ .. t+2 in entries 0 .. NQ-1
+    // read while q of plane p+1 is formed, used for f of that plane in the next iteration: the
+    // advective and diffusive terms of the plane's own four faces, and the cell's own values at
+    // planes p and p+1 (so no plane's neighbours are read from LDS twice); the same for E2
+    T e_adv[2] = {T(0), T(0)}, e_dif[2] = {T(0), T(0)}, e_c0[2] = {T(0), T(0)}, e_c1[2] = {T(0), T(0)};
+    T adv2 = T(0), dif2 = T(0), m_p0 = T(0), m_c0 = T(0), m_c1 = T(0), m_c2 = T(0);
+    // own-cell queues from E1 to E2: after E1 of iteration t they hold planes t+3-NQ .. t+2 in entries
+    // 0 .. NQ-1 (U and V, which E1 and E2 both use one plane ahead: t+4-NQ .. t+3)
     T qa_phi[NQ] = {}, qa_acc[NQ] = {}, qa_u0[NQ] = {}, qa_u1[NQ] = {}, qa_v0[NQ] = {};
     T qa_v1[NQ] = {}, qa_w1[NQ] = {};
 
@@ -401,7 +397,7 @@ __device__ __forceinline__ void fused_body(const FusedArgs<T>& a, int ti, int tj
         fetch_in(tbeg + 4);
         commit_in(0);
         if (STAGE) {
-            fetch_vel(tbeg + 2);
+            fetch_vel(tbeg + 3);
             commit_vel(0);
         }
         if (SWEEP_B) {
@@ -410,7 +406,7 @@ __device__ __forceinline__ void fused_body(const FusedArgs<T>& a, int ti, int tj
             eacc_pre = facc.load(wrapz(tbeg + 2, nz), e_col[0]);
         }
         fetch_in(tbeg + 5);
-        if (STAGE) fetch_vel(tbeg + 3);
+        if (STAGE) fetch_vel(tbeg + 4);
         if (SWEEP_B) fetch_b(tbeg + 3);
         __syncthreads();
     } else {
@@ -419,7 +415,7 @@ __device__ __forceinline__ void fused_body(const FusedArgs<T>& a, int ti, int tj
         fetch_in(tbeg + 3);
         commit_in(1);
         fetch_in(tbeg + 4);
-        if (STAGE) fetch_vel(tbeg + 2);
+        if (STAGE) fetch_vel(tbeg + 3);
         if (SWEEP_B) fetch_b(tbeg + 2);
     }
 
@@ -437,22 +433,23 @@ __device__ __forceinline__ void fused_body(const FusedArgs<T>& a, int ti, int tj
         if constexpr (LAG) {
             // the planes of the next iteration into the slots this one does not read
             commit_in((R + 1) % 4);  // plane t+5
-            if (STAGE) commit_vel((R + 1) % 2);  // velocities of plane t+3 (W: t+4)
+            if (STAGE) commit_vel((R + 1) % 2);  // velocities of plane t+4
             if (SWEEP_B) commit_b((R + 1) % 2);
             fetch_in(t + 6);
-            if (STAGE) fetch_vel(t + 4);
+            if (STAGE) fetch_vel(t + 5);
             if (SWEEP_B) fetch_b(t + 4);
         } else {
             commit_in(sc);
-            if (STAGE) commit_vel(0);  // velocities of plane t+2 (W: t+3)
+            if (STAGE) commit_vel(0);  // velocities of plane t+3
             if (SWEEP_B) commit_b(0);
             fetch_in(t + 5);
-            if (STAGE) fetch_vel(t + 3);
+            if (STAGE) fetch_vel(t + 4);
             if (SWEEP_B) fetch_b(t + 3);
         }
-        // E1 operands from global memory (plane p = t+2), issued before the barrier; the
-        // accumulator is read at the wrapped plane (it is used on the domain's planes only)
-        const int pw = mapz(t + 2), pa = wrapz(t + 2, nz), pa1 = wrapz(t + 3, nz);
+        // E1 operands from global memory (the velocities of plane t+3, the accumulator of plane
+        // t+2), issued before the barrier; the accumulator is read at the wrapped plane (it is used
+        // on the domain's planes only)
+        const int pw = mapz(t + 3), pa = wrapz(t + 2, nz), pa1 = wrapz(t + 3, nz);
         int pw1;
         const int sgw = wface(t + 3, pw1);
         T eu0[2], eu1[2], ev0[2], ev1[2], ew1[2], eacc = T(0);
@@ -515,22 +512,31 @@ __device__ __forceinline__ void fused_body(const FusedArgs<T>& a, int ti, int tj
         const T* Q1Yo = s_q1y + q1old * Q1YS;
         T* YM = s_mid + sa * MS;  // ya at plane t+2
 
-        // q1 at plane t+3 on the E1 slots and the outer ring
-        T qzn[2];
+        // q1 at plane t+3 on the E1 slots and the outer ring; the terms of that plane's own four
+        // faces for the next iteration (n_adv, n_dif)
+        T qzn[2], n_adv[2], n_dif[2], n_c[2];
 #pragma unroll
         for (int s = 0; s < 2; ++s) {
-            if (s == 1 && !has_ring) {
-                qzn[s] = T(0);
-                continue;
-            }
+            qzn[s] = n_adv[s] = n_dif[s] = n_c[s] = T(0);
+            if (s == 1 && !has_ring) continue;
             const int oi = (e_lx[s] + 2) + (e_ly[s] + 2) * INW;
-            const T gx = grad1(IB[oi + 1], IB[oi - 1], inv_2dx);
-            const T gy = grad1(IB[oi + INW], IB[oi - INW], inv_2dx);
-            const T gz = grad1(IC[oi], IA[oi], inv_2dx);
-            const T fac = sharpen_factor(IB[oi], gx, gy, gz, d2, hg);
+            if constexpr (R == 0 && !WITH_E2) {  // the march's first iteration: nothing handed down yet
+                e_c0[s] = IA[oi];
+                e_c1[s] = IB[oi];
+            }
+            const T pc = e_c1[s];
+            n_c[s] = IC[oi];
+            const T pxm = IB[oi - 1], pxp = IB[oi + 1], pym = IB[oi - INW], pyp = IB[oi + INW];
+            const T gx = grad1(pxp, pxm, inv_2dx);
+            const T gy = grad1(pyp, pym, inv_2dx);
+            const T gz = grad1(n_c[s], e_c0[s], inv_2dx);
+            const T fac = sharpen_factor(pc, gx, gy, gz, d2, hg);
             Q1Xn[(e_lx[s] + 1) + e_ly[s] * Q1XW] = fac * gx;
             Q1Yn[e_lx[s] + (e_ly[s] + 1) * MW] = fac * gy;
             qzn[s] = fac * gz;
+            n_adv[s] = plane_adv(face_sum(pxm, pc), face_sum(pc, pxp), face_sum(pym, pc), face_sum(pc, pyp),
+                                 eu0[s], eu1[s], ev0[s], ev1[s]);
+            n_dif[s] = plane_dif(face_diff(pxm, pc), face_diff(pc, pxp), face_diff(pym, pc), face_diff(pc, pyp));
         }
         if (has_out) {
             const T gx = grad1(IB[o_in + 1], IB[o_in - 1], inv_2dx);
@@ -547,18 +553,12 @@ __device__ __forceinline__ void fused_body(const FusedArgs<T>& a, int ti, int tj
         for (int s = 0; s < 2; ++s) {
             if (s == 1 && !has_ring) continue;
             const int lx = e_lx[s], ly = e_ly[s];
-            const int oi = (lx + 2) + (ly + 2) * INW;
-            const T pc = IA[oi];
-            const T pz = IB[oi];
+            const T pc = e_c0[s], pz = e_c1[s];
             const T szp = face_sum(pc, pz), dzp = face_diff(pc, pz);
             const T* qx = Q1Xo + lx + ly * Q1XW;  // q1_x at lx-1, lx, lx+1
             const T* qy = Q1Yo + lx + ly * MW;     // q1_y at ly-1, ly, ly+1 (stride MW)
-            const T pxm = IA[oi - 1], pxp = IA[oi + 1], pym = IA[oi - INW], pyp = IA[oi + INW];
-            const T f1 = cell_rhs(face_sum(pxm, pc), face_sum(pc, pxp), face_sum(pym, pc),
-                                  face_sum(pc, pyp), e_sz[s], szp, face_diff(pxm, pc),
-                                  face_diff(pc, pxp), face_diff(pym, pc), face_diff(pc, pyp), e_dz[s],
-                                  dzp, qx[0], qx[2], qy[0], qy[2 * MW], e_qzm[s], qzn[s], eu0[s],
-                                  eu1[s], ev0[s], ev1[s], e_w0[s], ew1[s], a.nhs1, ge);
+            const T f1 = finish_rhs(e_adv[s], e_dif[s], e_sz[s], szp, e_dz[s], dzp, qx[0], qx[2], qy[0],
+                                    qy[2 * MW], e_qzm[s], qzn[s], e_w0[s], ew1[s], a.nhs1, ge);
             const T base = SWEEP_B ? s_pb[vs * PBS + (WIDE ? lx + 2 : lx) + ly * PBW] : pc;
             const T ym = fma(a.c_mid, f1, base);
             YM[lx + ly * MW] = ym;
@@ -567,7 +567,7 @@ __device__ __forceinline__ void fused_body(const FusedArgs<T>& a, int ti, int tj
                     const int p = t + 2;
                     if (a.out_mid && p >= k0 && p < k1 && active) fomid.store(p, e_col[0], ym);
                 }
-                // own cell: hand plane p's values to E2 (used two iterations later)
+                // own cell: hand the values to E2 (used two iterations later)
 #pragma unroll
                 for (int q = 0; q < NQ - 1; ++q) {
                     qa_phi[q] = qa_phi[q + 1];
@@ -585,12 +585,22 @@ __device__ __forceinline__ void fused_body(const FusedArgs<T>& a, int ti, int tj
                 qa_v0[NQ - 1] = ev0[0];
                 qa_v1[NQ - 1] = ev1[0];
                 qa_w1[NQ - 1] = ew1[0];
+                if constexpr (!WALLS) {  // (a ghost cell takes its partner's value below)
+                    m_p0 = m_c0;
+                    m_c0 = m_c1;
+                    m_c1 = m_c2;
+                    m_c2 = ym;
+                }
             }
             e_sz[s] = szp;
             e_dz[s] = dzp;
             e_qzm[s] = e_qz[s];
             e_qz[s] = qzn[s];
             e_w0[s] = ew1[s];
+            e_adv[s] = n_adv[s];
+            e_dif[s] = n_dif[s];
+            e_c0[s] = e_c1[s];
+            e_c1[s] = n_c[s];
         }
         if constexpr (WALLS) if (wx || wy) {
             __syncthreads();  // every E1 value of plane t+2 is in YM
@@ -616,14 +626,22 @@ __device__ __forceinline__ void fused_body(const FusedArgs<T>& a, int ti, int tj
             const T* M2 = s_mid + m2 * MS;
             constexpr int q2new = LAG ? R & 1 : (R + 1) & 1, q2old = LAG ? (R + 1) & 1 : R & 1;
             const int om = (tx + 2) + (ty + 2) * MW;
-            const T pc1 = M1[om];
-            const T gx = grad1(M1[om + 1], M1[om - 1], inv_2dx);
-            const T gy = grad1(M1[om + MW], M1[om - MW], inv_2dx);
-            const T gz = grad1(M2[om], M0[om], inv_2dx);
+            // the cell's own middle values at planes to, to+1 and to+2 (without walls this thread
+            // has computed them; LAG: the last one is that of the previous iteration)
+            const T pc = WALLS ? M0[om] : (LAG ? m_p0 : m_c0), pc1 = WALLS ? M1[om] : (LAG ? m_c0 : m_c1);
+            const T pc2 = WALLS ? M2[om] : (LAG ? m_c1 : m_c2);
+            const T pxm = M1[om - 1], pxp = M1[om + 1], pym = M1[om - MW], pyp = M1[om + MW];
+            const T gx = grad1(pxp, pxm, inv_2dx);
+            const T gy = grad1(pyp, pym, inv_2dx);
+            const T gz = grad1(pc2, pc, inv_2dx);
             const T fac = sharpen_factor(pc1, gx, gy, gz, d2, hg);
             s_q2x[q2new * Q2XS + (tx + 1) + ty * Q2XW] = fac * gx;
             s_q2y[q2new * Q2YS + tx + (ty + 1) * TX] = fac * gy;
             T q2zn = fac * gz;
+            const T adv2n = plane_adv(face_sum(pxm, pc1), face_sum(pc1, pxp), face_sum(pym, pc1),
+                                      face_sum(pc1, pyp), qa_u0[0], qa_u1[0], qa_v0[0], qa_v1[0]);
+            const T dif2n = plane_dif(face_diff(pxm, pc1), face_diff(pc1, pxp), face_diff(pym, pc1),
+                                      face_diff(pc1, pyp));
             if constexpr (WALLS) {  // walled z: the ghost planes next to the walls mirror exactly
                 if (wz && to + 1 == 0) q2z = -q2zn;   // plane -1, from plane 0
                 if (wz && to + 1 == nz) q2zn = -q2z;  // plane nz, from plane nz-1
@@ -638,18 +656,12 @@ __device__ __forceinline__ void fused_body(const FusedArgs<T>& a, int ti, int tj
                 else
                     s_q2y[q2new * Q2YS + h_dst] = hf * hgy;
             }
-            const T pc = M0[om];
             const T szp = face_sum(pc, pc1), dzp = face_diff(pc, pc1);
             if (to >= k0 && to < k1 && active) {
                 const T* qx = s_q2x + q2old * Q2XS + tx + ty * Q2XW;
                 const T* qy = s_q2y + q2old * Q2YS + tx + ty * TX;
-                const T pxm = M0[om - 1], pxp = M0[om + 1], pym = M0[om - MW], pyp = M0[om + MW];
-                const T f2 = cell_rhs(face_sum(pxm, pc), face_sum(pc, pxp), face_sum(pym, pc),
-                                      face_sum(pc, pyp), sz2, szp, face_diff(pxm, pc),
-                                      face_diff(pc, pxp), face_diff(pym, pc), face_diff(pc, pyp),
-                                      dz2, dzp, qx[0], qx[2], qy[0], qy[2 * TX], q2zm, q2zn,
-                                      qa_u0[0], qa_u1[0], qa_v0[0], qa_v1[0], w2, qa_w1[0], a.nhs2,
-                                      ge);
+                const T f2 = finish_rhs(adv2, dif2, sz2, szp, dz2, dzp, qx[0], qx[2], qy[0], qy[2 * TX], q2zm,
+                                        q2zn, w2, qa_w1[0], a.nhs2, ge);
                 const unsigned c = e_col[0];  // own cell (i0+tx, j0+ty): no wrap when active
                 if (!SWEEP_B) foy.store(to, c, fma(a.c_y2, f2, qa_phi[0]));
                 if constexpr (XOUT && !SWEEP_B)
@@ -661,6 +673,8 @@ __device__ __forceinline__ void fused_body(const FusedArgs<T>& a, int ti, int tj
             q2zm = q2z;
             q2z = q2zn;
             w2 = qa_w1[0];
+            adv2 = adv2n;
+            dif2 = dif2n;
         }
         if constexpr (LAG) __syncthreads();  // the iteration's LDS writes visible to the next
     };
@@ -673,34 +687,34 @@ __device__ __forceinline__ void fused_body(const FusedArgs<T>& a, int ti, int tj
         iteration(IntC<2>(), IntC<0>(), tbeg + 2);
         iteration(IntC<3>(), IntC<0>(), tbeg + 3);
         iteration(IntC<0>(), IntC<0>(), tbeg + 4);
-        const int tend = k0 - 1 + 4 * ((k1 - k0 + 5) / 4);  // k0-1 .. k1, in groups of four
-        for (int t = k0 - 1; t < tend; t += 4) {
+        for (int t = k0 - 1;; t += 4) {  // k0-1 .. k1
             iteration(IntC<1>(), IntC<1>(), t);
-            if (EXITS && t + 1 > k1) break;
+            if (t + 1 > k1) break;
             iteration(IntC<2>(), IntC<1>(), t + 1);
-            if (EXITS && t + 2 > k1) break;
+            if (t + 2 > k1) break;
             iteration(IntC<3>(), IntC<1>(), t + 2);
-            if (EXITS && t + 3 > k1) break;
+            if (t + 3 > k1) break;
             iteration(IntC<0>(), IntC<1>(), t + 3);
+            if (t + 4 > k1) break;
         }
     } else {
         iteration(IntC<0>(), IntC<0>(), tbeg);
         iteration(IntC<1>(), IntC<0>(), tbeg + 1);
         iteration(IntC<2>(), IntC<0>(), tbeg + 2);
         iteration(IntC<3>(), IntC<0>(), tbeg + 3);
-        const int tend = k0 - 2 + 6 * ((k1 - k0 + 7) / 6);  // k0-2 .. k1-1, in groups of six
-        for (int t = k0 - 2; t < tend; t += 6) {
+        for (int t = k0 - 2;; t += 6) {  // k0-2 .. k1-1
             iteration(IntC<4>(), IntC<1>(), t);
-            if (EXITS && t + 1 >= k1) break;
+            if (t + 1 >= k1) break;
             iteration(IntC<5>(), IntC<1>(), t + 1);
-            if (EXITS && t + 2 >= k1) break;
+            if (t + 2 >= k1) break;
             iteration(IntC<0>(), IntC<1>(), t + 2);
-            if (EXITS && t + 3 >= k1) break;
+            if (t + 3 >= k1) break;
             iteration(IntC<1>(), IntC<1>(), t + 3);
-            if (EXITS && t + 4 >= k1) break;
+            if (t + 4 >= k1) break;
             iteration(IntC<2>(), IntC<1>(), t + 4);
-            if (EXITS && t + 5 >= k1) break;
+            if (t + 5 >= k1) break;
             iteration(IntC<3>(), IntC<1>(), t + 5);
+            if (t + 6 >= k1) break;
         }
     }
 }

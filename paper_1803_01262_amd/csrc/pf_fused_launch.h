@@ -12,8 +12,7 @@ namespace pf {
 // FP64 needs more registers than that and runs at two waves per SIMD.
 // XOUT: the optional outputs (out_mid; sweep A also out_phi). WALLS: x and/or y walled (a.walls),
 // element-wise plane loads, single-descriptor addressing.
-template <typename T, int TX, int TY, bool SWEEP_B, bool BIG, bool WIDE, bool XOUT, bool WALLS = false,
-          bool EXITS = false>
+template <typename T, int TX, int TY, bool SWEEP_B, bool BIG, bool WIDE, bool XOUT, bool WALLS = false>
 __global__ void __launch_bounds__(TX* TY) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 4 : 2)))
 fused_kernel(FusedArgs<T> a, int tiles_x, int tiles_y, int kz)
 {
@@ -22,30 +21,30 @@ fused_kernel(FusedArgs<T> a, int tiles_x, int tiles_y, int kz)
     b /= tiles_x;
     const int tj = b % tiles_y;
     const int k0 = (b / tiles_y) * kz;
-    fused_body<T, TX, TY, SWEEP_B, BIG, WIDE, XOUT, WALLS, fused_lag<T, TX, TY>(), EXITS>(
+    fused_body<T, TX, TY, SWEEP_B, BIG, WIDE, XOUT, WALLS, fused_lag<T, TX, TY>()>(
         a, ti, tj, k0, min(k0 + kz, a.nz));
 }
 
-template <typename T, int TX, int TY, bool BIG, bool WIDE, bool WALLS = false, bool EXITS = false>
+template <typename T, int TX, int TY, bool BIG, bool WIDE, bool WALLS = false>
 hipError_t launch_fused_sweep(const FusedArgs<T>& a, bool sweep_b, unsigned blocks, int tiles_x,
                               int tiles_y, int kz, hipStream_t st)
 {
     if (sweep_b) {
         if constexpr (!WALLS) {  // sweep B with out_mid: periodic x and y only
             if (a.out_mid) {
-                hipLaunchKernelGGL((fused_kernel<T, TX, TY, true, BIG, WIDE, true, false, EXITS>),
+                hipLaunchKernelGGL((fused_kernel<T, TX, TY, true, BIG, WIDE, true, false>),
                                    dim3(blocks), dim3(TX * TY), 0, st, a, tiles_x, tiles_y, kz);
                 return hipGetLastError();
             }
         }
         if (a.out_mid || a.out_phi) return hipErrorInvalidValue;
-        hipLaunchKernelGGL((fused_kernel<T, TX, TY, true, BIG, WIDE, false, WALLS, EXITS>), dim3(blocks),
+        hipLaunchKernelGGL((fused_kernel<T, TX, TY, true, BIG, WIDE, false, WALLS>), dim3(blocks),
                            dim3(TX * TY), 0, st, a, tiles_x, tiles_y, kz);
     } else if (a.out_mid || a.out_phi)
-        hipLaunchKernelGGL((fused_kernel<T, TX, TY, false, BIG, WIDE, true, WALLS, EXITS>), dim3(blocks),
+        hipLaunchKernelGGL((fused_kernel<T, TX, TY, false, BIG, WIDE, true, WALLS>), dim3(blocks),
                            dim3(TX * TY), 0, st, a, tiles_x, tiles_y, kz);
     else
-        hipLaunchKernelGGL((fused_kernel<T, TX, TY, false, BIG, WIDE, false, WALLS, EXITS>), dim3(blocks),
+        hipLaunchKernelGGL((fused_kernel<T, TX, TY, false, BIG, WIDE, false, WALLS>), dim3(blocks),
                            dim3(TX * TY), 0, st, a, tiles_x, tiles_y, kz);
     return hipGetLastError();
 }
@@ -59,29 +58,15 @@ static hipError_t launch_fused_form(const FusedArgs<T>& a, bool sweep_b, hipStre
     const int tiles_x = (a.nx + TX - 1) / TX, tiles_y = (a.ny + TY - 1) / TY;
     const long long tiles = (long long)tiles_x * tiles_y;
     int kz = KZ;
-    bool exits = false;
-    if constexpr (KZ == 0) {
-        // chunks below kExitPlanes take the march that leaves its last group at the chunk's end
-        // (us per step, whole groups / exits: FP32 112^3 56.7 / 47.3, 128^3 57.0 / 51.5, 512^3 (one
-        // chunk) 1937 / 1965; FP64 112^3 94.7 / 78.2, 128^3 95.8 / 89.5, 192^3 279 / 265). Sweeps A
-        // and B share the register budget, hence the residency, of their form.
-        constexpr int kExitPlanes = 64;
-        kz = launch_chunk_planes((const void*)fused_kernel<T, TX, TY, false, BIG, WIDE, false, WALLS, true>,
-                                 TX * TY, tiles, a.nz, 5, 1);
-        exits = kz < kExitPlanes;
-        if (!exits)
-            kz = launch_chunk_planes((const void*)fused_kernel<T, TX, TY, false, BIG, WIDE, false, WALLS, false>,
-                                     TX * TY, tiles, a.nz, 5);
+    if (KZ == 0) {
+        // sweeps A and B share the register budget, hence the residency, of their form
+        kz = launch_chunk_planes((const void*)fused_kernel<T, TX, TY, false, BIG, WIDE, false, WALLS>, TX * TY,
+                                 tiles, a.nz, 5, 1);
         if (kz <= 0) return hipErrorInvalidDevice;
     }
     const long long blocks = tiles * ((a.nz + kz - 1) / kz);
     if (blocks <= 0 || blocks > 0x7fffffffLL) return hipErrorInvalidValue;
-    if constexpr (KZ == 0)
-        if (exits)
-            return launch_fused_sweep<T, TX, TY, BIG, WIDE, WALLS, true>(a, sweep_b, (unsigned)blocks, tiles_x,
-                                                                         tiles_y, kz, st);
-    return launch_fused_sweep<T, TX, TY, BIG, WIDE, WALLS, false>(a, sweep_b, (unsigned)blocks, tiles_x, tiles_y,
-                                                                  kz, st);
+    return launch_fused_sweep<T, TX, TY, BIG, WIDE, WALLS>(a, sweep_b, (unsigned)blocks, tiles_x, tiles_y, kz, st);
 }
 
 template <typename T, int TX, int TY, int KZ, bool FORCE_BIG>
