@@ -296,7 +296,8 @@ int32_t phasefield_solver_variant(const pf_solver *s);
  * two-stage sweeps per step, or four single-stage sweeps; for RK3, RK2 and Euler one
  * single-stage sweep per stage (Euler then one batched copy of the accumulator into phi).
  * per_instance[0].variant selects the RK4 mode by its kind (a "fused_*" variant or a per-stage
- * one); with variant -1, FP32 runs fused and FP64 per-stage. Instances may have walls on any
+ * one); with variant -1, FP32 runs fused, FP64 too from about 4 M cells in all without walls, else
+ * per-stage. Instances may have walls on any
  * axes (each its own), in either mode; a scheme other than RK4 puts the batch in per-stage mode
  * (the fused sweeps pair RK4's stages).
  * The step sequence

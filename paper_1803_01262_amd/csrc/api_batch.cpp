@@ -18,6 +18,7 @@
 
 #include <algorithm>
 #include <cmath>
+#include <functional>
 #include <vector>
 
 #include "pf_api_internal.h"
@@ -83,57 +84,125 @@ static int B_stage_only(const pf_params* per_instance, int count)
     return 0;
 }
 
-// Mode: the kind (fused or per-stage) of the variant named by instance 0, else by dtype.
+// Mode: the kind (fused or per-stage) of the variant named by instance 0, else fused, but per-stage for
+// FP64 with walls (a walled 208 x 144 x 176 step takes 292 us in FP64 fused sweeps, 228 per stage)
+// and for FP64 batches that do not fill the device with fused tiles, one to a compute unit. us per 8
+// RK4 steps, fused / per-stage, by total cells: 0.08 M 462 / 422, 3.6 M 1347 / 1179, 5.9 M 2419 / 2479,
+// 8.4 M 2016 / 3296, 11.4 M 3654 / 4940, 29.8 M 8658 / 11935.
+constexpr long long kFusedMinCellsF64 = 1ll << 22;
 // Per-stage whenever the fused shapes do not apply (B_stage_only).
 static bool B_mode_fused(const pf_params* per_instance, int count)
 {
     if (B_stage_only(per_instance, count)) return false;
     const int dtype = per_instance[0].dtype, v0 = per_instance[0].variant;
     if (v0 >= 0 && v0 < stage_variant_count(dtype)) return variant_is_fused(dtype, v0);
-    return dtype == PF_F32;
+    if (dtype == PF_F32) return true;
+    long long cells = 0;
+    for (int b = 0; b < count; ++b) {
+        if (wall_mask(per_instance[b])) return false;
+        cells += (long long)per_instance[b].n[0] * per_instance[b].n[1] * per_instance[b].n[2];
+    }
+    return cells >= kFusedMinCellsF64;
 }
 
-// The global tile list. Instances are packed onto the 8 XCDs by longest processing time (largest
-// first, each onto the least-loaded XCD), so the tiles of one instance share one L2; within an
-// XCD's range the tiles run longest z-chunk first, so short tiles fill the end; the ranges are
-// padded to one length with empty entries (the launch maps workgroup ids onto the ranges).
-static bool build_tile_list(const pf_params* p, int count, int shape, std::vector<BatchTile>& out)
+// The global tile list for z-chunks of at most kz planes (an instance's chunks are as even as its
+// planes allow), and the iterations its longest XCD takes. A group of tiles, one chunk of an
+// instance, shares halos in x and y: groups (of at most one XCD's resident workgroups each) are
+// packed onto the 8 XCDs by longest processing time, so their halos meet in one L2. Within an XCD's
+// range the tiles run longest first, so short tiles fill the end; the ranges are padded to one length
+// with empty entries (the launch maps workgroup ids onto the ranges).
+static long long pack_tiles(const pf_params* p, int count, int shape, int slots, int kz,
+                            std::vector<BatchTile>* out)
 {
-    int TX, TY, KZ;
-    batch_tile_shape(shape, &TX, &TY, &KZ);
-    const int warm = shape != kBatchStage32x8 ? 6 : 2;  // warm-up planes per z-chunk
-    std::vector<double> work(count);
-    std::vector<int> order(count);
+    int TX, TY;
+    batch_tile_shape(shape, &TX, &TY);
+    // iterations of a tile: the fused marches warm up 6 planes, the per-stage ones 2 in groups of six
+    auto iterations = [&](int planes) { return shape != kBatchStage32x8 ? planes + 6 : 6 * ((planes + 7) / 6); };
+    struct Group {
+        int b, first, tiles, k0, planes;  // tiles first .. first + tiles - 1 of the chunk's column tiles
+    };
+    std::vector<Group> groups;
     for (int b = 0; b < count; ++b) {
-        const double tx = (p[b].n[0] + TX - 1) / TX, ty = (p[b].n[1] + TY - 1) / TY;
-        const double cz = (p[b].n[2] + KZ - 1) / KZ;
-        work[b] = tx * ty * ((double)p[b].n[2] + cz * warm);
-        order[b] = b;
+        const int n = p[b].n[2], chunks = (n + kz - 1) / kz;
+        const long long tiles = (long long)((p[b].n[0] + TX - 1) / TX) * ((p[b].n[1] + TY - 1) / TY);
+        for (int c = 0; c < chunks; ++c) {
+            const int k0 = (int)((long long)n * c / chunks), k1 = (int)((long long)n * (c + 1) / chunks);
+            for (long long f = 0; f < tiles; f += slots)
+                groups.push_back({b, (int)f, (int)std::min<long long>(slots, tiles - f), k0, k1 - k0});
+        }
     }
-    std::stable_sort(order.begin(), order.end(), [&](int x, int y) { return work[x] > work[y]; });
     constexpr int kXcd = 8;
-    std::vector<BatchTile> bins[kXcd];
-    double load[kXcd] = {0};
-    for (int b : order) {
+    std::stable_sort(groups.begin(), groups.end(), [&](const Group& u, const Group& v) {
+        return (long long)u.tiles * iterations(u.planes) > (long long)v.tiles * iterations(v.planes);
+    });
+    std::vector<Group> bins[kXcd];
+    long long load[kXcd] = {0};
+    size_t num[kXcd] = {0}, len = 0;
+    for (const Group& g : groups) {
         const int x = (int)(std::min_element(load, load + kXcd) - load);
-        load[x] += work[b];
-        const int tx = (p[b].n[0] + TX - 1) / TX, ty = (p[b].n[1] + TY - 1) / TY;
-        const int cz = (p[b].n[2] + KZ - 1) / KZ;
-        for (int k = 0; k < cz; ++k)
-            for (int j = 0; j < ty; ++j)
-                for (int i = 0; i < tx; ++i) bins[x].push_back({b, i, j, k});
+        load[x] += (long long)g.tiles * iterations(g.planes);
+        num[x] += g.tiles;
+        bins[x].push_back(g);
     }
-    size_t len = 0;
+    long long longest = 0;
     for (auto& bin : bins) {
-        std::stable_sort(bin.begin(), bin.end(), [&](const BatchTile& u, const BatchTile& v) {
-            return std::min(KZ, p[u.b].n[2] - u.tk * KZ) > std::min(KZ, p[v.b].n[2] - v.tk * KZ);
-        });
-        len = std::max(len, bin.size());
+        std::stable_sort(bin.begin(), bin.end(), [](const Group& u, const Group& v) { return u.planes > v.planes; });
+        // the dispatcher hands the next tile to the workgroup slot that is free first
+        std::vector<long long> slot(slots, 0);
+        for (const Group& g : bin)
+            for (int t = 0; t < g.tiles; ++t) {
+                std::pop_heap(slot.begin(), slot.end(), std::greater<long long>());
+                slot.back() += iterations(g.planes);
+                longest = std::max(longest, slot.back());
+                std::push_heap(slot.begin(), slot.end(), std::greater<long long>());
+            }
     }
-    if (len * kXcd > 0x7fffffffull) return false;
-    out.assign(len * kXcd, BatchTile{-1, 0, 0, 0});
-    for (int x = 0; x < kXcd; ++x) std::copy(bins[x].begin(), bins[x].end(), out.begin() + x * len);
-    return true;
+    if (out) {
+        for (size_t n : num) len = std::max(len, n);
+        if (len * kXcd > 0x7fffffffull) return -1;
+        out->assign(len * kXcd, BatchTile{-1, 0, 0, 0, 0});
+        for (int x = 0; x < kXcd; ++x) {
+            BatchTile* t = out->data() + x * len;
+            for (const Group& g : bins[x]) {
+                const int tx = (p[g.b].n[0] + TX - 1) / TX;
+                for (int e = g.first; e < g.first + g.tiles; ++e)
+                    *t++ = {g.b, e % tx, e / tx, (unsigned short)g.k0, (unsigned short)g.planes};
+            }
+        }
+    }
+    return longest;
+}
+
+// The tile list of a batch: the chunk length whose longest XCD finishes first. Long chunks repeat
+// less warm-up, short ones fill the device and even out the XCDs: 64 planes, whatever the batch,
+// left 40 instances of 32^3-128^3 (29.8 Mcells) at 5.38 ms per 8 FP32 RK4 steps, the choice here
+// (48) takes 4.90; 12 FP64 instances of 32^3-96^3 2.62 / 1.18 ms, 8 of 16^3-32^3 1.06 / 0.42. Ties go to the longer chunk; lists of more than 20000 64-plane tiles take 64 planes.
+static pf_status build_tile_list(const pf_params* p, int count, int shape, std::vector<BatchTile>& out)
+{
+    bool walls = false;
+    long long columns = 0;
+    int TX, TY;
+    batch_tile_shape(shape, &TX, &TY);
+    for (int b = 0; b < count; ++b) {
+        walls = walls || wall_mask(p[b]) != 0;
+        columns += (long long)((p[b].n[0] + TX - 1) / TX) * ((p[b].n[1] + TY - 1) / TY) * ((p[b].n[2] + 63) / 64);
+    }
+    const int slots = batch_slots_per_xcd(shape, p[0].dtype, walls);
+    if (slots <= 0) return fail(PF_ERR_DEVICE, "no device to size the batch for");
+    int best_kz = 64;
+    if (columns <= 20000) {
+        long long best = -1;
+        for (int kz : {128, 96, 64, 48, 32, 24, 16, 12, 8}) {
+            const long long t = pack_tiles(p, count, shape, slots, kz, nullptr);
+            if (best < 0 || t < best) {
+                best = t;
+                best_kz = kz;
+            }
+        }
+    }
+    if (pack_tiles(p, count, shape, slots, best_kz, &out) < 0)
+        return fail(PF_ERR_INVALID, "the batch has too many tiles for one launch");
+    return PF_OK;
 }
 
 extern "C" pf_status phasefield_batch_create(const pf_params* per_instance, int32_t count,
@@ -158,8 +227,8 @@ extern "C" pf_status phasefield_batch_create(const pf_params* per_instance, int3
     }
     std::vector<BatchTile> list;
     const int shape = B_mode_fused(per_instance, count) ? kBatchFused32x16 : kBatchStage32x8;
-    if (!build_tile_list(per_instance, count, shape, list))
-        return fail(PF_ERR_INVALID, "the batch has too many tiles for one launch");
+    const pf_status ls = build_tile_list(per_instance, count, shape, list);
+    if (ls != PF_OK) return ls;
     auto* B = new pf_batch();
     B->count = count;
     B->dtype = per_instance[0].dtype;
@@ -389,8 +458,8 @@ static pf_status batch_apply_shape(pf_batch* b, int shape)
 {
     if (shape == b->shape) return PF_OK;
     std::vector<BatchTile> list;
-    if (!build_tile_list(b->p.data(), b->count, shape, list))
-        return fail(PF_ERR_INVALID, "the batch has too many tiles for one launch");
+    const pf_status ls = build_tile_list(b->p.data(), b->count, shape, list);
+    if (ls != PF_OK) return ls;
     hipError_t e = b->key_stream ? hipStreamSynchronize(b->key_stream) : hipDeviceSynchronize();
     if (e != hipSuccess) return hip_fail(e, "phasefield_batch_set_shape: synchronize");
     batch_release_graph(b);

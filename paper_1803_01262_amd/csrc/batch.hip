@@ -8,10 +8,9 @@
 namespace pf {
 
 // Tile shapes (BatchShape): fused 32x16 (instances down to 32 cells wide), fused 64x8 (fewer
-// halo columns where rows are whole multiples of 64), per-stage 32x8; 64-plane z-chunks (little
-// warm-up per chunk; 96 and 128 planes measured no faster).
-constexpr int kBTX = 32, kBTY = 8, kBKZ = 64;   // per-stage tile
-constexpr int kFKZ = 64;                        // fused tiles' z-chunk
+// halo columns where rows are whole multiples of 64), per-stage 32x8; the z-chunks come with the
+// tile list.
+constexpr int kBTX = 32, kBTY = 8;  // per-stage tile
 
 // Workgroup -> tile-list entry: the list holds 8 equal ranges of `len` entries, one per XCD.
 // One workgroup per entry: xcd_tile_order lets each XCD walk its own range in order.
@@ -39,7 +38,7 @@ __device__ __forceinline__ void for_batch_tiles(const BatchTile* __restrict__ ti
 // An instance's arguments in the constant address space (the tables are written before the launch
 // and never during it), so that the march reads them with scalar loads wherever it needs them: read
 // through an ordinary pointer they are held in vector registers across its barriers and stores, and
-// the FP32 sweep B spilled 12 of them (40 instances of 32^3-128^3: BATCHNUM ms per 8 steps).
+// the FP32 sweep B spilled 12 of them (40 instances of 32^3-128^3: 4.97 / 4.17 ms per 8 steps with / without).
 template <typename A>
 using ConstArgs = const __attribute__((address_space(4))) A;
 template <typename A>
@@ -54,11 +53,9 @@ __global__ void __launch_bounds__(kBTX* kBTY) batch_stage_kernel(const StageArgs
                                                                   int len)
 {
     for_batch_tiles<PERSIST>(tiles, len, [&](const BatchTile& tl) {
-        const int k0 = tl.tk * kBKZ;
-        // 64-plane chunks: the form that loads per-cell operands one iteration ahead (1.6-1.8 %
-        // faster)
-        tiled_stage_body<T, kBTX, kBTY, false, WALLS, true>(args[tl.b], tl.ti, tl.tj, k0,
-                                                            min(k0 + kBKZ, args[tl.b].nz));
+        // the form that loads per-cell operands one iteration ahead (1.6-1.8 % faster on 64-plane
+        // chunks)
+        tiled_stage_body<T, kBTX, kBTY, false, WALLS, true>(args[tl.b], tl.ti, tl.tj, tl.k0, tl.k0 + tl.planes);
     });
 }
 
@@ -71,11 +68,11 @@ __global__ void __launch_bounds__(TX* TY) __attribute__((amdgpu_waves_per_eu(siz
 batch_fused_kernel(const FusedArgs<T>* __restrict__ args, const BatchTile* __restrict__ tiles, int len)
 {
     for_batch_tiles<PERSIST>(tiles, len, [&](const BatchTile& tl) {
-        const int k0 = __builtin_amdgcn_readfirstlane(tl.tk) * kFKZ;
+        const int k0 = __builtin_amdgcn_readfirstlane((int)tl.k0);
         auto& a = const_args(args, tl.b);
         fused_body<T, TX, TY, SWEEP_B, false, WIDE, false, WALLS, fused_lag<T, TX, TY>()>(
             a, __builtin_amdgcn_readfirstlane(tl.ti), __builtin_amdgcn_readfirstlane(tl.tj), k0,
-            min(k0 + kFKZ, a.nz));
+            k0 + __builtin_amdgcn_readfirstlane((int)tl.planes));
     });
 }
 
@@ -88,11 +85,33 @@ __global__ void batch_copy_kernel(const BatchCopy<T>* __restrict__ e)
         c.dst[i] = c.src[i];
 }
 
-void batch_tile_shape(int shape, int* tx, int* ty, int* kz)
+void batch_tile_shape(int shape, int* tx, int* ty)
 {
     *tx = shape == kBatchFused64x8 ? 64 : 32;
     *ty = shape == kBatchFused32x16 ? 16 : 8;
-    *kz = shape == kBatchStage32x8 ? kBKZ : kFKZ;
+}
+
+template <typename T>
+static int batch_groups_per_cu(int shape, bool walls)
+{
+    // sweeps A and B, with and without 16-byte loads, have the same register budget and LDS residency
+    const void* k;
+    if (shape == kBatchStage32x8)
+        k = walls ? (const void*)batch_stage_kernel<T, false, true> : (const void*)batch_stage_kernel<T, false, false>;
+    else if (shape == kBatchFused64x8)
+        k = walls ? (const void*)batch_fused_kernel<T, 64, 8, true, false, false, true>
+                  : (const void*)batch_fused_kernel<T, 64, 8, true, false, false, false>;
+    else
+        k = walls ? (const void*)batch_fused_kernel<T, 32, 16, true, false, false, true>
+                  : (const void*)batch_fused_kernel<T, 32, 16, true, false, false, false>;
+    return resident_groups_per_cu(k, shape == kBatchStage32x8 ? kBTX * kBTY : 512);
+}
+
+int batch_slots_per_xcd(int shape, int dtype, bool walls)
+{
+    const int groups = dtype == PF_F32 ? batch_groups_per_cu<float>(shape, walls)
+                                       : batch_groups_per_cu<double>(shape, walls);
+    return device_compute_units() / 8 * groups;
 }
 
 // Grid of the persistent form: the resident slots of the kernel (compute units x workgroups per

@@ -242,10 +242,15 @@ __device__ __forceinline__ void fused_body(Args& a, int ti, int tj, int k0, int 
             o_axis = 1;
         }
     }
-    // ---- q2 halo cell (threads at the top of the block, which have no ring work)
+    // ---- q2 halo cell (threads at the top of the block, which have no ring work). Where no thread
+    // has both kinds of halo cell, the two share their registers (with them apart, the batched FP32
+    // sweep B spilled one in its loop: 40 instances of 32^3-128^3, 4.90 -> 4.43 ms per 8 steps)
+    constexpr bool ONE_HALO = OUT0 + NOUT <= NT - NH2;
     const int rh = tid - (NT - NH2);
     const bool has_h2 = rh >= 0;
-    int h_om = 0, h_dst = 0, h_axis = 0;
+    int h_own[3] = {0, 0, 0};
+    int &h_om = ONE_HALO ? o_in : h_own[0], &h_dst = ONE_HALO ? o_dst : h_own[1];
+    int& h_axis = ONE_HALO ? o_axis : h_own[2];
     if (has_h2) {
         if (rh < 2 * TY) {
             const int side = rh / TY, r = rh - side * TY;
@@ -371,10 +376,10 @@ __device__ __forceinline__ void fused_body(Args& a, int ti, int tj, int k0, int 
     };
 
     // per-slot z state of E1 at plane p: q1_z at p-1 and p, sum and difference of phi on the
-    // face (p-1, p), W at p; the same for E2 at plane t
+    // face (p-1, p), W at p; the same for E2 at plane t (of that face only the value at t-1)
     T e_qzm[2] = {T(0), T(0)}, e_qz[2] = {T(0), T(0)}, e_sz[2] = {T(0), T(0)};
     T e_dz[2] = {T(0), T(0)}, e_w0[2] = {T(0), T(0)};
-    T q2zm = T(0), q2z = T(0), sz2 = T(0), dz2 = T(0), w2 = T(0);
+    T q2zm = T(0), q2z = T(0), m_prev = T(0), w2 = T(0);
     // read while q of plane p+1 is formed, used for f of that plane in the next iteration: the
     // advective and diffusive terms of the plane's own four faces, and the cell's own values at
     // planes p and p+1 (so no plane's neighbours are read from LDS twice); the same for E2
@@ -660,16 +665,15 @@ __device__ __forceinline__ void fused_body(Args& a, int ti, int tj, int k0, int 
             if (to >= k0 && to < k1 && active) {
                 const T* qx = s_q2x + q2old * Q2XS + tx + ty * Q2XW;
                 const T* qy = s_q2y + q2old * Q2YS + tx + ty * TX;
-                const T f2 = finish_rhs(adv2, dif2, sz2, szp, dz2, dzp, qx[0], qx[2], qy[0], qy[2 * TX], q2zm,
-                                        q2zn, w2, qa_w1[0], a.nhs2, ge);
+                const T f2 = finish_rhs(adv2, dif2, face_sum(m_prev, pc), szp, face_diff(m_prev, pc), dzp, qx[0],
+                                        qx[2], qy[0], qy[2 * TX], q2zm, q2zn, w2, qa_w1[0], a.nhs2, ge);
                 const unsigned c = e_col[0];  // own cell (i0+tx, j0+ty): no wrap when active
                 if (!SWEEP_B) foy.store(to, c, fma(a.c_y2, f2, qa_phi[0]));
                 if constexpr (XOUT && !SWEEP_B)
                     if (a.out_phi) fophi.store(to, c, qa_phi[0]);
                 if (SWEEP_B || a.out_acc) foacc.store(to, c, fma(a.c_acc2, f2, qa_acc[0]));
             }
-            sz2 = szp;
-            dz2 = dzp;
+            m_prev = pc;
             q2zm = q2z;
             q2z = q2zn;
             w2 = qa_w1[0];

@@ -251,10 +251,12 @@ int stage_variant_index(int dtype, const char* name);
 
 // ------------------------------------------------------------------ batched stages (batch.hip)
 // Per-instance arguments of one sweep (per-stage mode: StageArgs, fused mode: FusedArgs), and the
-// global tile list: one entry {instance, ti, tj, tk} per workgroup, instance < 0 for the padding
-// entries that even out the per-XCD ranges (they do nothing).
+// global tile list: one entry per workgroup, the column tile (ti, tj) of instance b and its planes
+// [k0, k0 + planes); b < 0 for the padding entries that even out the per-XCD ranges (they do
+// nothing).
 struct BatchTile {
-    int b, ti, tj, tk;
+    int b, ti, tj;
+    unsigned short k0, planes;  // n[2] <= 65535
 };
 template <typename T>
 struct BatchCopy {
@@ -280,8 +282,10 @@ template <typename T>
 hipError_t launch_batch_copy(const BatchCopy<T>* table_dev, int count, hipStream_t st);
 // Tile shapes of the batched sweeps (the values of phasefield_batch_set_shape).
 enum BatchShape { kBatchFused32x16 = 0, kBatchFused64x8 = 1, kBatchStage32x8 = 2, kNumBatchShapes = 3 };
-// Tile of a batch shape: x, y extent and z-chunk.
-void batch_tile_shape(int shape, int* tx, int* ty, int* kz);
+// Tile of a batch shape: x and y extent.
+void batch_tile_shape(int shape, int* tx, int* ty);
+// Workgroups of a shape's sweep resident on one XCD of the current device; 0 on error.
+int batch_slots_per_xcd(int shape, int dtype, bool walls);
 
 // ------------------------------------------------------------------ adjoint (adjoint.hip)
 // Tiled z-march with tile shape `tile` (an index from adjoint_tile_index or
