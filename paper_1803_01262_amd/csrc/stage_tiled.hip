@@ -359,8 +359,9 @@ int default_stage_variant(int nx, int ny, int nz, int dtype)
 // bricks: FP32 32^3 20.6 / 10.4, 64^3 21.8 / 13.2, 96^3 29.6 / 25.9, 128^3 49.8 / 49.1, 160^3 68 /
 // 88; FP64 32^3 21.7 / 11.6, 64^3 26.0 / 15.4, 96^3 35.6 / 32.1, 128^3 64.0 / 63.2, 160^3 102 /
 // 121; walls on x and z FP64 80^3 36.7 / 24.5, 128^3 71.5 / 68.2), and less on a non-uniform one,
-// whose tables every brick reads again (RK4: FP32 64^3 33.1 / 21.4, 112^3 75.8 / 66.5, 128^3 85 /
-// 91; FP64 64^3 38.3 / 27.4, 96^3 81 / 74, 112^3 101 / 109). One-plane grids have their own kernel.
+// whose tables every brick reads again (RK4, widest-cell eps: FP32 64^3 31.2 / 21.3, 96^3 47.4 /
+// 46.1, 104^3 70.5 / 61.8, 112^3 72 / 72, march alone at 128^3 79.5; FP64 64^3 37.0 / 27.3, 96^3 74.8 /
+// 74.3, march alone at 112^3 92.5). One-plane grids have their own kernel.
 bool stage_takes_bricks(int nx, int ny, int nz, int dtype, bool nu)
 {
     const long long n = !nu ? 128 : dtype == PF_F32 ? 118 : 102;
