@@ -297,8 +297,7 @@ int32_t phasefield_solver_variant(const pf_solver *s);
  * single-stage sweep per stage (Euler then one batched copy of the accumulator into phi).
  * per_instance[0].variant selects the RK4 mode by its kind (a "fused_*" variant or a per-stage
  * one); with variant -1, FP32 runs fused, FP64 too from about 4 M cells in all without walls, else
- * per-stage. Instances may have walls on any
- * axes (each its own), in either mode; a scheme other than RK4 puts the batch in per-stage mode
+ * per-stage. Instances may have walls on any axes (each its own), in either mode; a scheme other than RK4 puts the batch in per-stage mode
  * (the fused sweeps pair RK4's stages).
  * The step sequence
  * is replayed from a captured HIP graph. Results are bit-identical to running each instance

@@ -381,7 +381,7 @@ int stage_brick_variant(int nx, int ny, int nz, int dtype)
 // / 8x8x4 / 8x8x8 / 16x8x8 bricks / single stages on 16x8x4: FP32 32^3 27.7 / 11.0 / 13.0 / 14.7 /
 // 13.6, 48^3 28.7 / 14.5 / 13.3 / 15.7 / 14.3, 64^3 29.4 / 23.7 / 20.3 / 16.7 / 17.5, 80^3 35.1 /
 // 33.3 / 30.0 / 25.1 / 24.5, 96^3 40.0 / 53 / 48 / 39.1 / 34.9, 112^3 56.6 / - / - / - / 49.2, 128^3
-// 57.1 (51.3 now) / - / - / - / 66.2; FP64 32^3 29.7 / 13.5 / 16.1 / - / 15.4, 48^3 33.8 / 20.4 / 17.7 / - /
+// 57.1 (47.2 now) / - / - / - / 66.2; FP64 32^3 29.7 / 13.5 / 16.1 / - / 15.4, 48^3 33.8 / 20.4 / 17.7 / - /
 // 16.4, 64^3 35.0 / 34.6 / 32.3 / - / 20.8, 96^3 50.6 / - / - / - / 44.8, 128^3 95.5 / - / - / - /
 // 89.3, 160^3 152 / - / - / - / 170). Element-wise loads (walls) reach that point earlier (FP32,
 // walls on x and z: 48^3 8x8x8 15.0, single stages 15.7; 64^3 16x8x8 20.5, single stages 19.3).
