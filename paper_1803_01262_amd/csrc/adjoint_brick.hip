@@ -17,140 +17,102 @@ namespace pf {
 template <typename T, int BX, int BY, int BZ, bool WALLS, bool FAST>
 __global__ void __launch_bounds__(BX* BY* BZ) adjoint_brick_kernel(AdjArgs<T> a, int tiles_x, int tiles_y)
 {
-    constexpr int NT = BX * BY * BZ;
-    constexpr int IX = BX + 4, IY = BY + 4, IZ = BZ + 4, IXY = IX * IY, IS = IXY * IZ;
-    constexpr int NL = (IS + NT - 1) / NT;
-    constexpr int GXS = (BX + 2) * BY * BZ, GYS = BX * (BY + 2) * BZ, GZS = BX * BY * (BZ + 2);
-    constexpr int NH = 2 * (BY * BZ + BX * BZ + BX * BY), NHS = (NH + NT - 1) / NT;
-    static_assert(IS < 8192 && SmallDiv<IX>::exact(0, IS) && SmallDiv<IY>::exact(0, IY * IZ),
-                  "the small divisions are exact over their ranges");
-    __shared__ T sy[IS];
-    __shared__ T sk[IS];
-    __shared__ T sgx[GXS];
-    __shared__ T sgy[GYS];
-    __shared__ T sgz[GZS];
+    using Frame = BrickFrame<BX, BY, BZ, WALLS, FAST>;
+    constexpr int IX = Frame::IX, IXY = Frame::IXY;
+    __shared__ T sy[Frame::IS];
+    __shared__ T sk[Frame::IS];
+    __shared__ T sgx[(BX + 2) * BY * BZ];
+    __shared__ T sgy[BX * (BY + 2) * BZ];
+    __shared__ T sgz[BX * BY * (BZ + 2)];
 
-    const int nx = a.nx, ny = a.ny, nz = a.nz;
-    int b = xcd_tile_order(blockIdx.x, gridDim.x);
-    const int ti = b % tiles_x;
-    b /= tiles_x;
-    const int i0 = ti * BX, j0 = (b % tiles_y) * BY, k0 = (b / tiles_y) * BZ;
-    const int tid = threadIdx.x;
-    const bool wx = WALLS && (a.walls & 1), wy = WALLS && (a.walls & 2), wz = WALLS && (a.walls & 4);
-    auto mapx = [&](int v) { return wx ? brick_mirror<FAST>(v, nx) : brick_wrap<FAST>(v, nx); };
-    auto mapy = [&](int v) { return wy ? brick_mirror<FAST>(v, ny) : brick_wrap<FAST>(v, ny); };
-    auto mapz = [&](int v) { return wz ? brick_mirror<FAST>(v, nz) : brick_wrap<FAST>(v, nz); };
+    const Frame fr(a.nx, a.ny, a.nz, a.walls, tiles_x, tiles_y);
     constexpr unsigned ES = sizeof(T);
-    const unsigned whole = (unsigned)((size_t)nx * ny * nz * ES);
-    const rsrc_t ry = plane_rsrc(a.y, whole), rk = plane_rsrc(a.kap_in, whole);
-    auto at = [&](int x, int y, int z) { return ((unsigned)(z * ny + y) * (unsigned)nx + (unsigned)x) * ES; };
-
-    T py[NL], pk[NL];
-#pragma unroll
-    for (int s = 0; s < NL; ++s) {
-        const int e = tid + s * NT;
-        if (IS % NT == 0 || e < IS) {
-            const int row = SmallDiv<IX>::div(e), x = e - row * IX, z = SmallDiv<IY>::div(row), y = row - z * IY;
-            const unsigned off = at(mapx(i0 - 2 + x), mapy(j0 - 2 + y), mapz(k0 - 2 + z));
-            py[s] = bload<T>(ry, off);
-            pk[s] = bload<T>(rk, off);
-        }
-    }
-    const int x = tid % BX, y = tid / BX % BY, z = tid / (BX * BY);
-    const int i = i0 + x, j = j0 + y, k = k0 + z;
+    T py[Frame::NL], pk[Frame::NL];
+    fr.for_input([&](int s, int e, int kw, unsigned o) {
+        py[s] = ldg(a.y + kw * fr.plane, o * ES);
+        pk[s] = ldg(a.kap_in + kw * fr.plane, o * ES);
+    });
+    const int nx = a.nx, ny = a.ny, nz = a.nz, x = fr.x, y = fr.y, z = fr.z;
+    const int i = fr.i0 + x, j = fr.j0 + y, k = fr.k0 + z;
     const bool active = i < nx && j < ny && k < nz;
-    const unsigned c = active ? at(i, j, k) : 0u;
+    const unsigned c = fr.at(i, j) * ES;
+    const size_t kp = k * fr.plane;
     T u0 = T(0), u1 = T(0), v0 = T(0), v1 = T(0), w0 = T(0), w1 = T(0), gu = T(0), gv = T(0), gw = T(0), lb = T(0),
       lp = T(0);
     if (active) {
-        u0 = ldg(a.U, c);
-        u1 = ldg(a.U, at(i + 1 == nx ? 0 : i + 1, j, k));
-        v0 = ldg(a.V, c);
-        v1 = ldg(a.V, at(i, j + 1 == ny ? 0 : j + 1, k));
-        w0 = ldg(a.W, c);
-        w1 = ldg(a.W, at(i, j, k + 1 == nz ? 0 : k + 1));
-        if (a.gU) gu = ldg(a.gU, c);
-        if (a.gV) gv = ldg(a.gV, c);
-        if (a.gW) gw = ldg(a.gW, c);
-        if (a.lam_out) lb = ldg(a.lam_base, c);
-        if (a.kap_out) lp = ldg(a.lamp, c);
+        u0 = ldg(a.U + kp, c);
+        u1 = ldg(a.U + kp, i + 1 == nx ? c - (unsigned)(nx - 1) * ES : c + ES);
+        v0 = ldg(a.V + kp, c);
+        v1 = ldg(a.V + kp, j + 1 == ny ? (unsigned)i * ES : c + (unsigned)nx * ES);
+        w0 = ldg(a.W + kp, c);
+        w1 = ldg(a.W + (k + 1 == nz ? 0 : k + 1) * fr.plane, c);
+        if (a.gU) gu = ldg(a.gU + kp, c);
+        if (a.gV) gv = ldg(a.gV + kp, c);
+        if (a.gW) gw = ldg(a.gW + kp, c);
+        if (a.lam_out) lb = ldg(a.lam_base + kp, c);
+        if (a.kap_out) lp = ldg(a.lamp + kp, c);
     }
-#pragma unroll
-    for (int s = 0; s < NL; ++s) {
-        const int e = tid + s * NT;
-        if (IS % NT == 0 || e < IS) {
-            sy[e] = py[s];
-            sk[e] = a.kap_scale * pk[s];
-        }
-    }
+    fr.for_input([&](int s, int e, int, unsigned) {
+        sy[e] = py[s];
+        sk[e] = a.kap_scale * pk[s];
+    });
     __syncthreads();
 
     const T inv_dx = a.inv_dx, inv_2dx = a.inv_2dx, d2 = a.delta2, hs = a.hs, hg = a.hg, ge = a.ge;
-    auto cell = [&](int q, T gb[3]) -> T {  // gbar and the local term of the cell at offset q
+    // the cell at offset q: the cotangent's terms f of its six faces, its gradient cotangent gb and, as
+    // the result, its local term
+    auto cell = [&](int q, T f[6], T gb[3]) -> T {
         const T *Y = sy + q, *K = sk + q;
-        T g[3], qb[3];
-        g[0] = grad1(Y[1], Y[-1], inv_2dx);
-        g[1] = grad1(Y[IX], Y[-IX], inv_2dx);
-        g[2] = grad1(Y[IXY], Y[-IXY], inv_2dx);
-        qb[0] = -hg * (adj_face(K[-1], K[0], inv_dx) + adj_face(K[0], K[1], inv_dx));
-        qb[1] = -hg * (adj_face(K[-IX], K[0], inv_dx) + adj_face(K[0], K[IX], inv_dx));
-        qb[2] = -hg * (adj_face(K[-IXY], K[0], inv_dx) + adj_face(K[0], K[IXY], inv_dx));
+        const T kc = K[0];
+        const T g[3] = {grad1(Y[1], Y[-1], inv_2dx), grad1(Y[IX], Y[-IX], inv_2dx), grad1(Y[IXY], Y[-IXY], inv_2dx)};
+        f[0] = adj_face(K[-1], kc, inv_dx);
+        f[1] = adj_face(kc, K[1], inv_dx);
+        f[2] = adj_face(K[-IX], kc, inv_dx);
+        f[3] = adj_face(kc, K[IX], inv_dx);
+        f[4] = adj_face(K[-IXY], kc, inv_dx);
+        f[5] = adj_face(kc, K[IXY], inv_dx);
+        const T qb[3] = {-hg * (f[0] + f[1]), -hg * (f[2] + f[3]), -hg * (f[4] + f[5])};
         return adj_cell(Y[0], g, qb, d2, gb);
     };
     const int o = (x + 2) + (y + 2) * IX + (z + 2) * IXY;
-    T gb[3];
-    const T loc = cell(o, gb);
+    T f[6], gb[3];  // f: kept for the gather
+    const T loc = cell(o, f, gb);
     sgx[(x + 1) + y * (BX + 2) + z * ((BX + 2) * BY)] = gb[0];
     sgy[x + (y + 1) * BX + z * (BX * (BY + 2))] = gb[1];
-    sgz[tid + BX * BY] = gb[2];
-#pragma unroll
-    for (int s = 0; s < NHS; ++s) {
-        int e = s * NT + (NT - 1 - tid);
-        if (e >= NH) continue;
-        T hb[3];
-        if (e < 2 * BY * BZ) {
-            const int side = e >= BY * BZ, t = e - side * (BY * BZ), hy = t % BY, hz = t / BY;
-            (void)cell((side ? BX + 2 : 1) + (hy + 2) * IX + (hz + 2) * IXY, hb);
-            sgx[(side ? BX + 1 : 0) + hy * (BX + 2) + hz * ((BX + 2) * BY)] = hb[0];
-        } else if (e < 2 * BY * BZ + 2 * BX * BZ) {
-            e -= 2 * BY * BZ;
-            const int side = e >= BX * BZ, t = e - side * (BX * BZ), hx = t % BX, hz = t / BX;
-            (void)cell((hx + 2) + (side ? BY + 2 : 1) * IX + (hz + 2) * IXY, hb);
-            sgy[hx + (side ? BY + 1 : 0) * BX + hz * (BX * (BY + 2))] = hb[1];
-        } else {
-            e -= 2 * BY * BZ + 2 * BX * BZ;
-            const int side = e >= BX * BY, t = e - side * (BX * BY), hx = t % BX, hy = t / BX;
-            (void)cell((hx + 2) + (hy + 2) * IX + (side ? BZ + 2 : 1) * IXY, hb);
-            sgz[t + (side ? BZ + 1 : 0) * (BX * BY)] = hb[2];
-        }
-    }
+    sgz[x + y * BX + (z + 1) * (BX * BY)] = gb[2];
+    fr.for_halo([&](int, auto AXIS, int hx, int hy, int hz) {
+        constexpr int axis = decltype(AXIS)::value;
+        T hf[6], hb[3];
+        (void)cell((hx + 2) + (hy + 2) * IX + (hz + 2) * IXY, hf, hb);
+        if constexpr (axis == 0)
+            sgx[(hx + 1) + hy * (BX + 2) + hz * ((BX + 2) * BY)] = hb[0];
+        else if constexpr (axis == 1)
+            sgy[hx + (hy + 1) * BX + hz * (BX * (BY + 2))] = hb[1];
+        else
+            sgz[hx + hy * BX + (hz + 1) * (BX * BY)] = hb[2];
+    });
     __syncthreads();
     if (!active) return;
 
-    const T *Y = sy + o, *K = sk + o;
-    T ybar = loc;
-    T lo = adj_face(K[-1], K[0], inv_dx), hi = adj_face(K[0], K[1], inv_dx);
-    ybar = fma(lo, fma(-hs, u0, ge), ybar);
-    ybar = fma(hi, fma(-hs, u1, -ge), ybar);
-    if (a.gU) stg<T>(a.gU, c, fma(-hs * (Y[-1] + Y[0]), lo, gu));
+    const T* Y = sy + o;
     const T* GX = sgx + x + y * (BX + 2) + z * ((BX + 2) * BY);
-    ybar = fma(GX[0] - GX[2], inv_2dx, ybar);
-    lo = adj_face(K[-IX], K[0], inv_dx);
-    hi = adj_face(K[0], K[IX], inv_dx);
-    ybar = fma(lo, fma(-hs, v0, ge), ybar);
-    ybar = fma(hi, fma(-hs, v1, -ge), ybar);
-    if (a.gV) stg<T>(a.gV, c, fma(-hs * (Y[-IX] + Y[0]), lo, gv));
     const T* GY = sgy + x + y * BX + z * (BX * (BY + 2));
+    const T* GZ = sgz + x + y * BX + z * (BX * BY);
+    T ybar = loc;
+    ybar = fma(f[0], fma(-hs, u0, ge), ybar);
+    ybar = fma(f[1], fma(-hs, u1, -ge), ybar);
+    if (a.gU) stg<T>(a.gU + kp, c, fma(-hs * (Y[-1] + Y[0]), f[0], gu));
+    ybar = fma(GX[0] - GX[2], inv_2dx, ybar);
+    ybar = fma(f[2], fma(-hs, v0, ge), ybar);
+    ybar = fma(f[3], fma(-hs, v1, -ge), ybar);
+    if (a.gV) stg<T>(a.gV + kp, c, fma(-hs * (Y[-IX] + Y[0]), f[2], gv));
     ybar = fma(GY[0] - GY[2 * BX], inv_2dx, ybar);
-    lo = adj_face(K[-IXY], K[0], inv_dx);
-    hi = adj_face(K[0], K[IXY], inv_dx);
-    ybar = fma(lo, fma(-hs, w0, ge), ybar);
-    ybar = fma(hi, fma(-hs, w1, -ge), ybar);
-    if (a.gW) stg<T>(a.gW, c, fma(-hs * (Y[-IXY] + Y[0]), lo, gw));
-    const T* GZ = sgz + tid;
+    ybar = fma(f[4], fma(-hs, w0, ge), ybar);
+    ybar = fma(f[5], fma(-hs, w1, -ge), ybar);
+    if (a.gW) stg<T>(a.gW + kp, c, fma(-hs * (Y[-IXY] + Y[0]), f[4], gw));
     ybar = fma(GZ[0] - GZ[2 * BX * BY], inv_2dx, ybar);
-    if (a.lam_out) stg<T>(a.lam_out, c, lb + ybar);
-    if (a.kap_out) stg<T>(a.kap_out, c, fma(a.ka, ybar, a.kb * lp));
+    if (a.lam_out) stg<T>(a.lam_out + kp, c, lb + ybar);
+    if (a.kap_out) stg<T>(a.kap_out + kp, c, fma(a.ka, ybar, a.kb * lp));
 }
 
 template <typename T, int BX, int BY, int BZ>

@@ -1,4 +1,5 @@
-// What the brick kernels share (stage_brick.hip, adjoint_brick.hip): index arithmetic.
+// What the brick kernels share (stage_brick.hip, stage_brick1.hip, adjoint_brick.hip): index arithmetic,
+// and the frame of the two single-stage kernels.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -35,5 +36,115 @@ __device__ __forceinline__ int brick_mirror(int v, int n)
 {
     return FAST ? (v < 0 ? -1 - v : (v >= n ? 2 * n - 1 - v : v)) : reflectn(v, n);
 }
+
+// A brick of BX x BY x BZ cells, a thread to each cell, with a halo of two cells in LDS: the frame of
+// the single-stage kernels (one forward stage, one reverse stage). Beside the arithmetic of its cells
+// such a kernel mostly finds addresses, and where other work shares the device, so that no compute unit
+// idles, that is paid in full (vector issue bounds it then: alone, latency does). So everything along z
+// is scalar (a wave's elements lie in few planes, its own cells in one), the offsets to a cell's
+// neighbours are differences instead of products, and bricks whose halo stays inside the plane wrap
+// nothing. us per step alone / each of three at once on streams, every index in vector registers -> here:
+// RK3 96^3 FP32 26.1 / 18.1 -> 23.2 / 15.6, FP64 32.7 / 26.1 -> 31.1 / 23.5; RK4 with walls on x and z 96^3
+// FP32 38.6 / 26.5 -> 34.3 / 23.0, FP64 49.7 / 44.1 -> 45.7 / 39.7.
+template <int BX, int BY, int BZ, bool WALLS, bool FAST>
+struct BrickFrame {
+    static constexpr int NT = BX * BY * BZ, NW = NT / 64;
+    static constexpr int IX = BX + 4, IY = BY + 4, IZ = BZ + 4, IXY = IX * IY, IS = IXY * IZ;
+    // pieces of 64 elements: of an input plane, and per wave
+    static constexpr int CP = (IXY + 63) / 64, NL = (CP * IZ + NW - 1) / NW;
+    static constexpr int NH = 2 * (BY * BZ + BX * BZ + BX * BY), NHS = (NH + NT - 1) / NT;
+    static_assert(NT % 64 == 0 && BX * BY % 64 == 0, "a wave's own cells lie in one plane");
+    static_assert(IXY < 8192 && SmallDiv<IX>::exact(0, IXY), "the small division is exact over its range");
+
+    // An index of an axis: wrapped into it, or reflected at its walls. Within one period or image
+    // (FAST) both are (v ^ flip) + lo below 0 and (v ^ flip) + hi from n up, with flip = -1 at walls
+    // (~v = -1 - v) and the three in scalar registers.
+    struct Axis {
+        int n, flip, lo, hi;
+        __device__ __forceinline__ Axis(int n_, bool wall)
+            : n(n_), flip(wall ? -1 : 0), lo(wall ? 0 : n_), hi(wall ? 2 * n_ : -n_)
+        {
+        }
+        __device__ __forceinline__ int map(int v) const
+        {
+            if constexpr (!FAST) return flip ? reflectn(v, n) : wrapn(v, n);
+            const int t = WALLS ? v ^ flip : v;
+            const int r = v < 0 ? t + lo : v;  // one select after the other: no branches
+            return v >= n ? t + hi : r;
+        }
+    };
+    int nx, ny, nz, i0, j0, k0;
+    bool wx, wy, wz, inner;  // inner: the halo stays inside the plane
+    Axis ax, ay, az;
+    size_t plane;  // cells of a plane
+    int wave, lane;
+    int x, y, z;  // the thread's cell in the brick (z: scalar)
+
+    __device__ __forceinline__ BrickFrame(int nx_, int ny_, int nz_, int walls, int tiles_x, int tiles_y)
+        : nx(nx_), ny(ny_), nz(nz_), wx(WALLS && (walls & 1)), wy(WALLS && (walls & 2)), wz(WALLS && (walls & 4)),
+          ax(nx_, wx), ay(ny_, wy), az(nz_, wz), plane((size_t)nx_ * ny_)
+    {
+        int b = xcd_tile_order(blockIdx.x, gridDim.x);
+        const int ti = b % tiles_x;
+        b /= tiles_x;
+        i0 = ti * BX;
+        j0 = (b % tiles_y) * BY;
+        k0 = (b / tiles_y) * BZ;
+        inner = i0 >= 2 && i0 + BX + 2 <= nx && j0 >= 2 && j0 + BY + 2 <= ny;
+        wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+        lane = threadIdx.x & 63;
+        z = wave / (BX * BY / 64);
+        const int t = (wave % (BX * BY / 64)) * 64 + lane;
+        x = t % BX;
+        y = t / BX;
+    }
+    // an element of a plane (gx < 2^20, gy < 2^16, a plane below 2^28 cells)
+    __device__ __forceinline__ unsigned at(int gx, int gy) const { return __umul24((unsigned)gy, (unsigned)nx) + (unsigned)gx; }
+
+    // f(s, element in LDS, plane of the array, element of the plane) for the thread's elements
+    template <typename F>
+    __device__ __forceinline__ void for_input(F f) const
+    {
+        auto go = [&](auto IN) {
+#pragma unroll
+            for (int s = 0; s < NL; ++s) {
+                const unsigned c = (unsigned)wave * NL + s, zi = c / CP;
+                if (CP * IZ % NW != 0 && zi >= (unsigned)IZ) continue;
+                const int e = (int)(c - zi * CP) * 64 + lane;
+                if (IXY % 64 != 0 && e >= IXY) continue;
+                const int r = SmallDiv<IX>::div(e);
+                const int vx = i0 - 2 + e - r * IX, vy = j0 - 2 + r;
+                constexpr bool in = decltype(IN)::value != 0;
+                f(s, (int)zi * IXY + e, az.map(k0 - 2 + (int)zi), at(in ? vx : ax.map(vx), in ? vy : ay.map(vy)));
+            }
+        };
+        if (inner)
+            go(IntC<1>());
+        else
+            go(IntC<0>());
+    }
+    // f(s, axis, x, y, z) for the thread's cells next to the brick, from the last thread down
+    template <typename F>
+    __device__ __forceinline__ void for_halo(F f) const
+    {
+        constexpr int EX = 2 * BY * BZ, EY = EX + 2 * BX * BZ;
+        constexpr bool UNIFORM = EX % 64 == 0 && EY % 64 == 0 && NH % 64 == 0;  // a wave has one kind
+#pragma unroll
+        for (int s = 0; s < NHS; ++s) {
+            const int eb = s * NT + (NW - 1 - wave) * 64, e = eb + 63 - lane, q = UNIFORM ? eb : e;
+            if (q >= NH) continue;
+            if (q < EX) {
+                const int side = e >= BY * BZ, t = e - side * (BY * BZ);
+                f(s, IntC<0>(), side ? BX : -1, t % BY, t / BY);
+            } else if (q < EY) {
+                const int r = e - EX, side = r >= BX * BZ, t = r - side * (BX * BZ);
+                f(s, IntC<1>(), t % BX, side ? BY : -1, t / BX);
+            } else {
+                const int r = e - EY, side = r >= BX * BY, t = r - side * (BX * BY);
+                f(s, IntC<2>(), t % BX, t / BX, side ? BZ : -1);
+            }
+        }
+    }
+};
 
 }  // namespace pf

@@ -17,157 +17,106 @@ namespace pf {
 template <typename T, int BX, int BY, int BZ, bool WALLS, bool FAST, bool NU>
 __global__ void __launch_bounds__(BX* BY* BZ) stage_brick_kernel(StageArgs<T> a, int tiles_x, int tiles_y)
 {
-    constexpr int NT = BX * BY * BZ;
-    constexpr int IX = BX + 4, IY = BY + 4, IZ = BZ + 4, IXY = IX * IY, IS = IXY * IZ;
-    constexpr int NL = (IS + NT - 1) / NT;
-    constexpr int QXS = (BX + 2) * BY * BZ, QYS = BX * (BY + 2) * BZ, QZS = BX * BY * (BZ + 2);
-    constexpr int NH = 2 * (BY * BZ + BX * BZ + BX * BY), NHS = (NH + NT - 1) / NT;
-    static_assert(IS < 8192 && SmallDiv<IX>::exact(0, IS) && SmallDiv<IY>::exact(0, IY * IZ),
-                  "the small divisions are exact over their ranges");
-    __shared__ T sp[IS];
-    __shared__ T sqx[QXS];
-    __shared__ T sqy[QYS];
-    __shared__ T sqz[QZS];
+    using Frame = BrickFrame<BX, BY, BZ, WALLS, FAST>;
+    constexpr int IX = Frame::IX, IXY = Frame::IXY;
+    __shared__ T sp[Frame::IS];
+    __shared__ T sqx[(BX + 2) * BY * BZ];
+    __shared__ T sqy[BX * (BY + 2) * BZ];
+    __shared__ T sqz[BX * BY * (BZ + 2)];
 
-    const int nx = a.nx, ny = a.ny, nz = a.nz;
-    int b = xcd_tile_order(blockIdx.x, gridDim.x);
-    const int ti = b % tiles_x;
-    b /= tiles_x;
-    const int i0 = ti * BX, j0 = (b % tiles_y) * BY, k0 = (b / tiles_y) * BZ;
-    const int tid = threadIdx.x;
-    const bool wx = WALLS && (a.walls & 1), wy = WALLS && (a.walls & 2), wz = WALLS && (a.walls & 4);
-    auto mapx = [&](int v) { return wx ? brick_mirror<FAST>(v, nx) : brick_wrap<FAST>(v, nx); };
-    auto mapy = [&](int v) { return wy ? brick_mirror<FAST>(v, ny) : brick_wrap<FAST>(v, ny); };
-    auto mapz = [&](int v) { return wz ? brick_mirror<FAST>(v, nz) : brick_wrap<FAST>(v, nz); };
+    const Frame fr(a.nx, a.ny, a.nz, a.walls, tiles_x, tiles_y);
     constexpr unsigned ES = sizeof(T);
-    const rsrc_t ry = plane_rsrc(a.y, (unsigned)((size_t)nx * ny * nz * ES));
-    auto at = [&](int x, int y, int z) { return ((unsigned)(z * ny + y) * (unsigned)nx + (unsigned)x) * ES; };
-
-    T py[NL];
-#pragma unroll
-    for (int s = 0; s < NL; ++s) {
-        const int e = tid + s * NT;
-        if (IS % NT == 0 || e < IS) {
-            const int row = SmallDiv<IX>::div(e), x = e - row * IX, z = SmallDiv<IY>::div(row), y = row - z * IY;
-            py[s] = bload<T>(ry, at(mapx(i0 - 2 + x), mapy(j0 - 2 + y), mapz(k0 - 2 + z)));
-        }
-    }
-    const int x = tid % BX, y = tid / BX % BY, z = tid / (BX * BY);
-    const int i = i0 + x, j = j0 + y, k = k0 + z;
+    T py[Frame::NL];
+    fr.for_input([&](int s, int e, int kw, unsigned o) { py[s] = ldg(a.y + kw * fr.plane, o * ES); });
+    const int nx = a.nx, ny = a.ny, nz = a.nz, x = fr.x, y = fr.y, z = fr.z;
+    const int i = fr.i0 + x, j = fr.j0 + y, k = fr.k0 + z;
     const bool active = i < nx && j < ny && k < nz;
-    const unsigned c = active ? at(i, j, k) : 0u;
+    const unsigned c = fr.at(i, j) * ES;
+    const size_t kp = k * fr.plane;
     T u0 = T(0), u1 = T(0), v0 = T(0), v1 = T(0), w0 = T(0), w1 = T(0), b1 = T(0), b2 = T(0);
     if (active) {
-        u0 = ldg(a.U, c);
-        u1 = ldg(a.U, at(i + 1 == nx ? 0 : i + 1, j, k));
-        v0 = ldg(a.V, c);
-        v1 = ldg(a.V, at(i, j + 1 == ny ? 0 : j + 1, k));
-        w0 = ldg(a.W, c);
-        w1 = ldg(a.W, at(i, j, k + 1 == nz ? 0 : k + 1));
-        if (a.out1) b1 = ldg(a.base1, c);
-        if (a.out2) b2 = ldg(a.base2, c);
+        u0 = ldg(a.U + kp, c);
+        u1 = ldg(a.U + kp, i + 1 == nx ? c - (unsigned)(nx - 1) * ES : c + ES);
+        v0 = ldg(a.V + kp, c);
+        v1 = ldg(a.V + kp, j + 1 == ny ? (unsigned)i * ES : c + (unsigned)nx * ES);
+        w0 = ldg(a.W + kp, c);
+        w1 = ldg(a.W + (k + 1 == nz ? 0 : k + 1) * fr.plane, c);
+        if (a.out1) b1 = ldg(a.base1 + kp, c);
+        if (a.out2) b2 = ldg(a.base2 + kp, c);
         if constexpr (WALLS) {  // velocities on wall faces (index 0 of a walled axis)
-            if (wx && i == 0) u0 = T(0);
-            if (wx && i == nx - 1) u1 = T(0);
-            if (wy && j == 0) v0 = T(0);
-            if (wy && j == ny - 1) v1 = T(0);
-            if (wz && k == 0) w0 = T(0);
-            if (wz && k == nz - 1) w1 = T(0);
+            if (fr.wx && i == 0) u0 = T(0);
+            if (fr.wx && i == nx - 1) u1 = T(0);
+            if (fr.wy && j == 0) v0 = T(0);
+            if (fr.wy && j == ny - 1) v1 = T(0);
+            if (fr.wz && k == 0) w0 = T(0);
+            if (fr.wz && k == nz - 1) w1 = T(0);
         }
     }
-    // non-uniform mesh: column col of the tables at cell v of an axis
-    auto tab = [&](int axis, int v, int col) -> T {
-        const int m = axis == 0 ? mapx(v) : axis == 1 ? mapy(v) : mapz(v);
-        return a.nu[axis][m * kNuCols + col];
+    // non-uniform mesh: the row of an axis' table at cell v (adjacent columns: one load)
+    auto row = [&](int axis, int v) -> const T* {
+        const int m = axis == 0 ? fr.ax.map(v) : axis == 1 ? fr.ay.map(v) : fr.az.map(v);
+        return a.nu[axis] + m * kNuCols;
     };
     T sgx = a.inv_2dx, sgy = a.inv_2dx, sgz = a.inv_2dx;
     T nf[3][3], wd[3][3];  // per axis: 1/h, 1/distance across the low and the high face; the widths around
     if constexpr (NU) {
         const int v[3] = {i, j, k};
-        sgx = tab(0, i, kNuInvSpan);
-        sgy = tab(1, j, kNuInvSpan);
-        sgz = tab(2, k, kNuInvSpan);
+        T sg[3];
 #pragma unroll
         for (int ax = 0; ax < 3; ++ax) {
-            nf[ax][0] = tab(ax, v[ax], kNuInvW);
-            nf[ax][1] = tab(ax, v[ax], kNuInvDist);
-            nf[ax][2] = tab(ax, v[ax] + 1, kNuInvDist);  // the low face of the next cell
-#pragma unroll
-            for (int d = 0; d < 3; ++d) wd[ax][d] = tab(ax, v[ax] - 1 + d, kNuWidth);
+            const T *lo = row(ax, v[ax] - 1), *me = row(ax, v[ax]), *hi = row(ax, v[ax] + 1);
+            nf[ax][0] = me[kNuInvW];
+            sg[ax] = me[kNuInvSpan];
+            nf[ax][1] = me[kNuInvDist];
+            wd[ax][1] = me[kNuWidth];
+            nf[ax][2] = hi[kNuInvDist];  // the low face of the next cell
+            wd[ax][2] = hi[kNuWidth];
+            wd[ax][0] = lo[kNuWidth];
         }
+        sgx = sg[0];
+        sgy = sg[1];
+        sgz = sg[2];
     }
-#pragma unroll
-    for (int s = 0; s < NL; ++s) {
-        const int e = tid + s * NT;
-        if (IS % NT == 0 || e < IS) sp[e] = py[s];
-    }
+    T hc[Frame::NHS][3];  // gradient coefficients at the thread's cells next to the brick
+    if constexpr (NU)
+        fr.for_halo([&](int s, auto, int hx, int hy, int hz) {
+            hc[s][0] = row(0, fr.i0 + hx)[kNuInvSpan];
+            hc[s][1] = row(1, fr.j0 + hy)[kNuInvSpan];
+            hc[s][2] = row(2, fr.k0 + hz)[kNuInvSpan];
+        });
+    fr.for_input([&](int s, int e, int, unsigned) { sp[e] = py[s]; });
     __syncthreads();
 
     const T d2 = a.delta2, hg = NU ? a.nu_hg : a.hg;
-    auto sharpen = [&](int q, T cx, T cy, T cz, T g[3]) -> T {
-        const T* p = sp + q;
-        g[0] = grad1(p[1], p[-1], cx);
-        g[1] = grad1(p[IX], p[-IX], cy);
-        g[2] = grad1(p[IXY], p[-IXY], cz);
-        return sharpen_factor(p[0], g[0], g[1], g[2], d2, hg);
-    };
-    const int o = (x + 2) + (y + 2) * IX + (z + 2) * IXY;
+    // the cell and its neighbours, for the products here and the fluxes below
+    const T* p = sp + (x + 2) + (y + 2) * IX + (z + 2) * IXY;
+    const T pc = p[0], xm = p[-1], xp = p[1], ym = p[-IX], yp = p[IX], zm = p[-IXY], zp = p[IXY];
     {
-        T g[3];
-        const T fac = sharpen(o, sgx, sgy, sgz, g);
-        sqx[(x + 1) + y * (BX + 2) + z * ((BX + 2) * BY)] = fac * g[0];
-        sqy[x + (y + 1) * BX + z * (BX * (BY + 2))] = fac * g[1];
-        sqz[tid + BX * BY] = fac * g[2];
+        const T gx = grad1(xp, xm, sgx), gy = grad1(yp, ym, sgy), gz = grad1(zp, zm, sgz);
+        const T fac = sharpen_factor(pc, gx, gy, gz, d2, hg);
+        sqx[(x + 1) + y * (BX + 2) + z * ((BX + 2) * BY)] = fac * gx;
+        sqy[x + (y + 1) * BX + z * (BX * (BY + 2))] = fac * gy;
+        sqz[x + y * BX + (z + 1) * (BX * BY)] = fac * gz;
     }
-#pragma unroll
-    for (int s = 0; s < NHS; ++s) {
-        int e = s * NT + (NT - 1 - tid);
-        if (e >= NH) continue;
-        int hx, hy, hz, comp;  // the halo cell, relative to the brick
-        if (e < 2 * BY * BZ) {
-            const int side = e >= BY * BZ, t = e - side * (BY * BZ);
-            comp = 0;
-            hx = side ? BX : -1;
-            hy = t % BY;
-            hz = t / BY;
-        } else if (e < 2 * BY * BZ + 2 * BX * BZ) {
-            e -= 2 * BY * BZ;
-            const int side = e >= BX * BZ, t = e - side * (BX * BZ);
-            comp = 1;
-            hx = t % BX;
-            hy = side ? BY : -1;
-            hz = t / BX;
-        } else {
-            e -= 2 * BY * BZ + 2 * BX * BZ;
-            const int side = e >= BX * BY, t = e - side * (BX * BY);
-            comp = 2;
-            hx = t % BX;
-            hy = t / BX;
-            hz = side ? BZ : -1;
-        }
-        T cx = a.inv_2dx, cy = a.inv_2dx, cz = a.inv_2dx;
-        if constexpr (NU) {
-            cx = tab(0, i0 + hx, kNuInvSpan);
-            cy = tab(1, j0 + hy, kNuInvSpan);
-            cz = tab(2, k0 + hz, kNuInvSpan);
-        }
-        T g[3];
-        const T fac = sharpen((hx + 2) + (hy + 2) * IX + (hz + 2) * IXY, cx, cy, cz, g);
-        if (comp == 0)
-            sqx[(hx + 1) + hy * (BX + 2) + hz * ((BX + 2) * BY)] = fac * g[0];
-        else if (comp == 1)
-            sqy[hx + (hy + 1) * BX + hz * (BX * (BY + 2))] = fac * g[1];
+    fr.for_halo([&](int s, auto AXIS, int hx, int hy, int hz) {
+        constexpr int axis = decltype(AXIS)::value;
+        const T cx = NU ? hc[s][0] : a.inv_2dx, cy = NU ? hc[s][1] : a.inv_2dx, cz = NU ? hc[s][2] : a.inv_2dx;
+        const T* h = sp + (hx + 2) + (hy + 2) * IX + (hz + 2) * IXY;
+        const T g[3] = {grad1(h[1], h[-1], cx), grad1(h[IX], h[-IX], cy), grad1(h[IXY], h[-IXY], cz)};
+        const T q = sharpen_factor(h[0], g[0], g[1], g[2], d2, hg) * g[axis];
+        if constexpr (axis == 0)
+            sqx[(hx + 1) + hy * (BX + 2) + hz * ((BX + 2) * BY)] = q;
+        else if constexpr (axis == 1)
+            sqy[hx + (hy + 1) * BX + hz * (BX * (BY + 2))] = q;
         else
-            sqz[hx + hy * BX + (hz + 1) * (BX * BY)] = fac * g[2];
-    }
+            sqz[hx + hy * BX + (hz + 1) * (BX * BY)] = q;
+    });
     __syncthreads();
     if (!active) return;
 
-    const T* p = sp + o;
-    const T pc = p[0], xm = p[-1], xp = p[1], ym = p[-IX], yp = p[IX], zm = p[-IXY], zp = p[IXY];
     const T* QX = sqx + x + y * (BX + 2) + z * ((BX + 2) * BY);
     const T* QY = sqy + x + y * BX + z * (BX * (BY + 2));
-    const T* QZ = sqz + tid;
+    const T* QZ = sqz + x + y * BX + z * (BX * BY);
     T f;
     if constexpr (NU) {
         // diffusive coefficients of the six faces: gamma eps_face / centre distance
@@ -195,8 +144,8 @@ __global__ void __launch_bounds__(BX* BY* BZ) stage_brick_kernel(StageArgs<T> a,
                      face_diff(pc, yp), face_diff(zm, pc), face_diff(pc, zp), QX[0], QX[2], QY[0], QY[2 * BX],
                      QZ[0], QZ[2 * BX * BY], u0, u1, v0, v1, w0, w1, a.nhs, a.ge);
     }
-    if (a.out1) stg<T>(a.out1, c, fma(a.c1, f, b1));
-    if (a.out2) stg<T>(a.out2, c, fma(a.c2, f, b2));
+    if (a.out1) stg<T>(a.out1 + kp, c, fma(a.c1, f, b1));
+    if (a.out2) stg<T>(a.out2 + kp, c, fma(a.c2, f, b2));
 }
 
 template <typename T, int BX, int BY, int BZ, bool NU>
