@@ -28,9 +28,9 @@ __global__ void __launch_bounds__(BX* BY* BZ) adjoint_brick_kernel(AdjArgs<T> a,
     const Frame fr(a.nx, a.ny, a.nz, a.walls, tiles_x, tiles_y);
     constexpr unsigned ES = sizeof(T);
     T py[Frame::NL], pk[Frame::NL];
-    fr.for_input([&](int s, int e, int kw, unsigned o) {
-        py[s] = ldg(a.y + kw * fr.plane, o * ES);
-        pk[s] = ldg(a.kap_in + kw * fr.plane, o * ES);
+    fr.for_input([&](int s, int, size_t base, unsigned o) {
+        py[s] = ldg(a.y + base, o * ES);
+        pk[s] = ldg(a.kap_in + base, o * ES);
     });
     const int nx = a.nx, ny = a.ny, nz = a.nz, x = fr.x, y = fr.y, z = fr.z;
     const int i = fr.i0 + x, j = fr.j0 + y, k = fr.k0 + z;
@@ -52,7 +52,7 @@ __global__ void __launch_bounds__(BX* BY* BZ) adjoint_brick_kernel(AdjArgs<T> a,
         if (a.lam_out) lb = ldg(a.lam_base + kp, c);
         if (a.kap_out) lp = ldg(a.lamp + kp, c);
     }
-    fr.for_input([&](int s, int e, int, unsigned) {
+    fr.for_input([&](int s, int e, size_t, unsigned) {
         sy[e] = py[s];
         sk[e] = a.kap_scale * pk[s];
     });

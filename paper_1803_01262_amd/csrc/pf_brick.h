@@ -43,18 +43,20 @@ __device__ __forceinline__ int brick_mirror(int v, int n)
 // idles, that is paid in full (vector issue bounds it then: alone, latency does). So everything along z
 // is scalar (a wave's elements lie in few planes, its own cells in one), the offsets to a cell's
 // neighbours are differences instead of products, and bricks whose halo stays inside the plane wrap
-// nothing. us per step alone / each of three at once on streams, every index in vector registers -> here:
-// RK3 96^3 FP32 26.1 / 18.1 -> 23.2 / 15.6, FP64 32.7 / 26.1 -> 31.1 / 23.5; RK4 with walls on x and z 96^3
-// FP32 38.6 / 26.5 -> 34.3 / 23.0, FP64 49.7 / 44.1 -> 45.7 / 39.7.
+// nothing; a lane keeps its column of the input from piece to piece. us per step alone / each of three at
+// once on streams, every index in vector registers and the halo in pieces of 64 elements -> here:
+// RK3 96^3 FP32 26.1 / 18.0 -> 23.1 / 14.9, FP64 32.6 / 25.6 -> 30.7 / 22.7; RK4 with walls on x and z 96^3
+// FP32 38.6 / 26.4 -> 33.5 / 22.0, FP64 49.4 / 43.2 -> 44.3 / 37.9.
 template <int BX, int BY, int BZ, bool WALLS, bool FAST>
 struct BrickFrame {
     static constexpr int NT = BX * BY * BZ, NW = NT / 64;
     static constexpr int IX = BX + 4, IY = BY + 4, IZ = BZ + 4, IXY = IX * IY, IS = IXY * IZ;
-    // pieces of 64 elements: of an input plane, and per wave
-    static constexpr int CP = (IXY + 63) / 64, NL = (CP * IZ + NW - 1) / NW;
+    // an input plane in pieces of RP whole rows, a lane to each element: PP per plane, NL per wave
+    static constexpr int RP = 64 / IX, PP = IY / RP, NL = (PP * IZ + NW - 1) / NW;
     static constexpr int NH = 2 * (BY * BZ + BX * BZ + BX * BY), NHS = (NH + NT - 1) / NT;
     static_assert(NT % 64 == 0 && BX * BY % 64 == 0, "a wave's own cells lie in one plane");
-    static_assert(IXY < 8192 && SmallDiv<IX>::exact(0, IXY), "the small division is exact over its range");
+    static_assert(IY % RP == 0, "whole pieces");
+    static_assert(SmallDiv<IX>::exact(0, 64), "the small division is exact over its range");
 
     // An index of an axis: wrapped into it, or reflected at its walls. Within one period or image
     // (FAST) both are (v ^ flip) + lo below 0 and (v ^ flip) + hi from n up, with flip = -1 at walls
@@ -101,21 +103,25 @@ struct BrickFrame {
     // an element of a plane (gx < 2^20, gy < 2^16, a plane below 2^28 cells)
     __device__ __forceinline__ unsigned at(int gx, int gy) const { return __umul24((unsigned)gy, (unsigned)nx) + (unsigned)gx; }
 
-    // f(s, element in LDS, plane of the array, element of the plane) for the thread's elements
+    // f(s, element in LDS, element of the array as a scalar and a vector part) for the thread's elements
     template <typename F>
     __device__ __forceinline__ void for_input(F f) const
     {
+        if (RP * IX < 64 && lane >= RP * IX) return;
+        const int r = SmallDiv<IX>::div(lane), vx = i0 - 2 + lane - r * IX;
         auto go = [&](auto IN) {
+            constexpr bool in = decltype(IN)::value != 0;
+            const int gx = in ? vx : ax.map(vx);
 #pragma unroll
             for (int s = 0; s < NL; ++s) {
-                const unsigned c = (unsigned)wave * NL + s, zi = c / CP;
-                if (CP * IZ % NW != 0 && zi >= (unsigned)IZ) continue;
-                const int e = (int)(c - zi * CP) * 64 + lane;
-                if (IXY % 64 != 0 && e >= IXY) continue;
-                const int r = SmallDiv<IX>::div(e);
-                const int vx = i0 - 2 + e - r * IX, vy = j0 - 2 + r;
-                constexpr bool in = decltype(IN)::value != 0;
-                f(s, (int)zi * IXY + e, az.map(k0 - 2 + (int)zi), at(in ? vx : ax.map(vx), in ? vy : ay.map(vy)));
+                const int p = wave * NL + s, zi = p / PP, row = (p - zi * PP) * RP;
+                if (PP * IZ % NW != 0 && zi >= IZ) continue;
+                const size_t base = az.map(k0 - 2 + zi) * plane;
+                const int e = zi * IXY + row * IX + lane;
+                if constexpr (in)
+                    f(s, e, base + (size_t)(j0 - 2 + row) * nx, at(gx, r));
+                else
+                    f(s, e, base, at(gx, ay.map(j0 - 2 + row + r)));
             }
         };
         if (inner)

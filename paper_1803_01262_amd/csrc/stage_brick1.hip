@@ -27,7 +27,7 @@ __global__ void __launch_bounds__(BX* BY* BZ) stage_brick_kernel(StageArgs<T> a,
     const Frame fr(a.nx, a.ny, a.nz, a.walls, tiles_x, tiles_y);
     constexpr unsigned ES = sizeof(T);
     T py[Frame::NL];
-    fr.for_input([&](int s, int e, int kw, unsigned o) { py[s] = ldg(a.y + kw * fr.plane, o * ES); });
+    fr.for_input([&](int s, int, size_t base, unsigned o) { py[s] = ldg(a.y + base, o * ES); });
     const int nx = a.nx, ny = a.ny, nz = a.nz, x = fr.x, y = fr.y, z = fr.z;
     const int i = fr.i0 + x, j = fr.j0 + y, k = fr.k0 + z;
     const bool active = i < nx && j < ny && k < nz;
@@ -84,7 +84,7 @@ __global__ void __launch_bounds__(BX* BY* BZ) stage_brick_kernel(StageArgs<T> a,
             hc[s][1] = row(1, fr.j0 + hy)[kNuInvSpan];
             hc[s][2] = row(2, fr.k0 + hz)[kNuInvSpan];
         });
-    fr.for_input([&](int s, int e, int, unsigned) { sp[e] = py[s]; });
+    fr.for_input([&](int s, int e, size_t, unsigned) { sp[e] = py[s]; });
     __syncthreads();
 
     const T d2 = a.delta2, hg = NU ? a.nu_hg : a.hg;
