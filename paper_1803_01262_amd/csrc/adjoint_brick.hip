@@ -133,25 +133,28 @@ static hipError_t launch_adjoint_brick_shape(const AdjArgs<T>& a, hipStream_t st
 }
 
 // 16x8x4 bricks were the fastest shape at every size from 32^3 to 160^3 (8x8x8, 16x8x8, 16x16x4,
-// 32x8x4 and 16x4x4 were 0-60 % slower); large planes take 32x16x1 (the z halo of a 16x8x4 brick is
+// 32x8x4 and 16x4x4 were 0-60 % slower); large planes take 16x32x1 (the z halo of a 16x8x4 brick is
 // copies of the one plane).
 template <typename T>
 hipError_t launch_adjoint_brick(const AdjArgs<T>& a, hipStream_t st)
 {
-    if (a.nz == 1 && (long long)a.nx * a.ny > 362LL * 362) return launch_adjoint_brick_shape<T, 32, 16, 1>(a, st);
+    if (a.nz == 1 && (long long)a.nx * a.ny > 362LL * 362) return launch_adjoint_brick_shape<T, 16, 32, 1>(a, st);
     return launch_adjoint_brick_shape<T, 16, 8, 4>(a, st);
 }
 template hipError_t launch_adjoint_brick<float>(const AdjArgs<float>&, hipStream_t);
 template hipError_t launch_adjoint_brick<double>(const AdjArgs<double>&, hipStream_t);
 
-// us for the four reverse stages of an RK4 step, march / bricks: FP32 32^3 38.6 / 19.9, 64^3 42.4 /
-// 23.7, 96^3 58.5 / 49.2, 128^3 100.2 / 98.2, 160^3 165 / 178; FP64 32^3 41.9 / 20.3, 64^3 53.6 /
-// 31.8, 96^3 98.8 / 81.7, 112^3 146.6 / 117.9, 128^3 164 / 171, 160^3 380 / 454; one plane 64^2
-// FP64 35.8 / 19.9, 512^2 81 / 47.
-bool adjoint_takes_bricks(int nx, int ny, int nz, int dtype)
+// Up to 14 bricks of 16x8x4 per compute unit, where neither a grid alone on the device nor one beside
+// others loses more than the other gains (stage_takes_bricks; us per RK4 adjoint step alone / each of three
+// at once on streams, march -> bricks: FP32 64x72x101 (936 bricks) 71.8 / 33.6 -> 46.0 / 28.0, 112x88x116
+// (2233) 124.0 / 70.7 -> 80.4 / 59.8, 128x108x126 (3584) 130.0 / 101.9 -> 108.4 / 112.3, 128^3 (4096) 135.8 / 125.3 ->
+// 123.6 / 152.7; FP64 85.9 / 68.8 -> 63.8 / 45.6, 172.3 / 149.7 -> 118.7 / 143.6, 198.9 / 212.3 -> 180.6 / 232.4,
+// 120x97x145 (3848) 197.9 / 227.3 -> 182.7 / 261.1). One plane: us for the four reverse stages FP64 64^2 35.8 /
+// 19.9, 512^2 81 / 47.
+bool adjoint_takes_bricks(int nx, int ny, int nz)
 {
-    const long long n = dtype == PF_F32 ? 128 : 120;
-    return nz == 1 || (long long)nx * ny * nz <= n * n * n;
+    const long long bricks = (long long)((nx + 15) / 16) * ((ny + 7) / 8) * ((nz + 3) / 4);
+    return nz == 1 || bricks <= 14LL * device_compute_units();
 }
 
 }  // namespace pf

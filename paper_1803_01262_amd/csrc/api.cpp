@@ -196,7 +196,7 @@ static int walled_default_variant(int dtype, const int32_t n[3])
 {
     if (dtype == PF_F64) return per_stage_variant(n[0], n[1], n[2], dtype);
     const long long cells = (long long)n[0] * n[1] * n[2];
-    if (cells >= 144LL * 144 * 144) return stage_variant_index(dtype, "fused_32x16");
+    if (cells >= kWalledFusedMinCellsF32) return stage_variant_index(dtype, "fused_32x16");
     const bool x64 = (n[0] + 63) / 64 * 64 <= (n[0] + 31) / 32 * 32;
     return stage_variant_index(dtype, x64 ? "tiled_64x8" : "tiled_32x4");
 }

@@ -237,6 +237,8 @@ bool variant_is_fused(int dtype, int v);
 template <typename T>
 hipError_t launch_plane_step(const PlaneStepArgs<T>& a, int stages, hipStream_t st);
 int default_stage_variant(int nx, int ny, int nz, int dtype);
+// Walled FP32 grids from this many cells up take the fused sweeps (walled_default_variant).
+constexpr long long kWalledFusedMinCellsF32 = 144LL * 144 * 144;
 // Whether single stages of a grid run on bricks (handles whose variant was not named), and the
 // brick variant for them (-1: the handle's own).
 bool stage_takes_bricks(int nx, int ny, int nz, int dtype, bool nu);
@@ -302,7 +304,7 @@ hipError_t launch_adjoint_stage_nu(const AdjArgs<T>& a, hipStream_t st);  // non
 // One reverse stage on bricks (adjoint_brick.hip). Uniform meshes, arrays below 4 GiB.
 template <typename T>
 hipError_t launch_adjoint_brick(const AdjArgs<T>& a, hipStream_t st);
-bool adjoint_takes_bricks(int nx, int ny, int nz, int dtype);
+bool adjoint_takes_bricks(int nx, int ny, int nz);
 // Two reverse stages per launch (tile 0: 64x8, 1: 32x16; kz 0: chosen per launch). Arrays of
 // 4 GiB or more are refused (hipErrorInvalidValue): the caller runs single stages then.
 template <typename T>

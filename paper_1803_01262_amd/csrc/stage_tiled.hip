@@ -327,6 +327,9 @@ template hipError_t launch_stage_nu<double>(const StageArgs<double>&, bool, hipS
 constexpr long long kFusedMinCellsF32 = 104LL * 104 * 104;
 constexpr long long kFusedMinCellsF64 = 128LL * 128 * 128;
 constexpr long long kX64MinCellsF32 = 256LL * 256 * 256;
+// Above this many cells FP32 steps choose their fused tile by the march (auto_step_variant): single
+// stages on bricks lead up to here (us per RK4 step, bricks / fused: 104^3 39.8 / 41.1, 112^3 42.9 / 43.8, 128^3 57.7 / 47.0).
+constexpr long long kFusedTileMinCellsF32 = 108LL * 108 * 108 + 1;
 
 // Default variant before (or without) autotuning, from MI355X measurements at 32^3-640^3, all with
 // the chunk length chosen per launch: the fused sweeps (FP32 on 64x8 tiles unless those pad more
@@ -354,18 +357,28 @@ int default_stage_variant(int nx, int ny, int nz, int dtype)
                                       : per_stage_variant(nx, ny, nz, dtype);
 }
 
-// Single stages of small grids run on bricks (stage_brick1.hip): up to 128^3 cells on a uniform
-// mesh, where the march's tiles and chunks catch up with them (MI355X, us per RK3 step, march /
-// bricks: FP32 32^3 20.6 / 10.4, 64^3 21.8 / 13.2, 96^3 29.6 / 25.9, 128^3 49.8 / 49.1, 160^3 68 /
-// 88; FP64 32^3 21.7 / 11.6, 64^3 26.0 / 15.4, 96^3 35.6 / 32.1, 128^3 64.0 / 63.2, 160^3 102 /
-// 121; walls on x and z FP64 80^3 36.7 / 24.5, 128^3 71.5 / 68.2), and less on a non-uniform one,
-// whose tables every brick reads again (RK4, widest-cell eps: FP32 64^3 31.2 / 21.3, 96^3 47.4 /
-// 46.1, 104^3 70.5 / 61.8, 112^3 72 / 72, march alone at 128^3 79.5; FP64 64^3 37.0 / 27.3, 96^3 74.8 /
-// 74.3, march alone at 112^3 92.5). One-plane grids have their own kernel.
+static long long bricks_of(int nx, int ny, int nz, int bx, int by, int bz)
+{
+    return (long long)((nx + bx - 1) / bx) * ((ny + by - 1) / by) * ((nz + bz - 1) / bz);
+}
+
+// Single stages of small grids run on bricks (stage_brick1.hip). Alone on the device bricks lead far up:
+// a launch is mostly latency, and a march has more of it. Where other work fills the compute units the
+// halos that each brick loads and evaluates again count instead, and the march overtakes them earlier.
+// So the line, in bricks of 16x8x4 per compute unit, lies where neither use loses more than the other
+// gains (MI355X, us per step alone / each of three at once on streams, march -> bricks. RK3 FP32: 80x82x72
+// (990 bricks) 26.4 / 11.8 -> 16.7 / 9.1, 72x104x112 (1820) 33.3 / 17.8 -> 24.6 / 15.6, 112x105x114 (2842)
+// 40.5 / 24.0 -> 33.1 / 23.3, 116x115x108 (3240) 40.7 / 24.2 -> 36.0 / 26.6, 128^3 (4096) 49.9 / 31.4 -> 42.5 /
+// 33.4; FP64, the same grids: 30.8 / 15.4 -> 21.0 / 16.6, 39.7 / 27.4 -> 31.9 / 22.7, 54.9 / 34.1 -> 42.9 / 35.5,
+// 50.9 / 36.5 -> 46.7 / 44.5, 63.6 / 64.7 -> 57.1 / 70.1; RK4 with walls on x and z 104x105x110 (2744) FP32 59.7 /
+// 38.3 -> 46.0 / 38.6, FP64 83.4 / 47.4 -> 58.6 / 49.2). Lower on a non-uniform mesh, whose tables every brick
+// reads again (RK4, widest-cell eps, FP32: 74x92x80 (1200) 46.7 / 23.0 -> 32.6 / 20.2, 71x93x118 (1800) 53.4 /
+// 34.1 -> 44.1 / 29.8, 121x89x125 (3072) 72.3 / 34.8 -> 64.3 / 52.1; FP64 54.7 / 39.8 -> 49.4 / 35.9, 81x84x89
+// (1518) 55.8 / 42.2 -> 59.6 / 46.4). One-plane grids have their own kernel.
 bool stage_takes_bricks(int nx, int ny, int nz, int dtype, bool nu)
 {
-    const long long n = !nu ? 128 : dtype == PF_F32 ? 118 : 102;
-    return nz > 1 && (long long)nx * ny * nz <= n * n * n;
+    const int per_unit = !nu ? 11 : dtype == PF_F32 ? 8 : 5;
+    return nz > 1 && bricks_of(nx, ny, nz, 16, 8, 4) <= (long long)per_unit * device_compute_units();
 }
 
 int stage_brick_variant(int nx, int ny, int nz, int dtype)
@@ -374,40 +387,37 @@ int stage_brick_variant(int nx, int ny, int nz, int dtype)
 }
 
 // Whole RK4 and RK2 steps of small grids (and RK3 of one-plane grids): a brick variant, or -1 where
-// the grid's stage variant serves them. Two stages per brick while one brick per compute unit (or
-// two, FP32) covers the grid: a launch then takes one latency however few cells it has. From there
-// the halos that every such brick evaluates again cost more than the launches they save, and
-// single-stage bricks lead until the fused marches overtake them (MI355X, us per RK4 step, marches
-// / 8x8x4 / 8x8x8 / 16x8x8 bricks / single stages on 16x8x4: FP32 32^3 27.7 / 11.0 / 13.0 / 14.7 /
-// 13.6, 48^3 28.7 / 14.5 / 13.3 / 15.7 / 14.3, 64^3 29.4 / 23.7 / 20.3 / 16.7 / 17.5, 80^3 35.1 /
-// 33.3 / 30.0 / 25.1 / 24.5, 96^3 40.0 / 53 / 48 / 39.1 / 34.9, 112^3 56.6 / - / - / - / 49.2, 128^3
-// 57.1 (47.2 now) / - / - / - / 66.2; FP64 32^3 29.7 / 13.5 / 16.1 / - / 15.4, 48^3 33.8 / 20.4 / 17.7 / - /
-// 16.4, 64^3 35.0 / 34.6 / 32.3 / - / 20.8, 96^3 50.6 / - / - / - / 44.8, 128^3 95.5 / - / - / - /
-// 89.3, 160^3 152 / - / - / - / 170). Element-wise loads (walls) reach that point earlier (FP32,
-// walls on x and z: 48^3 8x8x8 15.0, single stages 15.7; 64^3 16x8x8 20.5, single stages 19.3).
+// the grid's stage variant serves them. Two stages per brick while one brick per compute unit covers the
+// grid: a launch then takes one latency however few cells it has. From there the halos that every such
+// brick evaluates again cost more than the launches they save, and single-stage bricks lead until the
+// marches overtake them (MI355X, us per RK4 step alone, marches / 8x8x4 / 8x8x8 / 16x8x8 / single stages on
+// 16x8x4: FP32 32^3 27.7 / 10.9 / 13.0 / 14.6 / 14.0, 40^3 28.6 / 11.6 / 13.1 / 17.1 / 14.3, 48^3 28.7 / 14.5 / 13.2 /
+// 15.8 / 14.1, 56x48x48 - / 14.9 / 13.6 / 16.3 / 16.2, 64x48x48 - / 19.7 / 19.4 / 16.1 / 16.1, 64^3 30.0 / 23.8 /
+// 20.4 / 16.7 / 16.9, 64x72x64 - / 26.1 / 24.7 / 23.2 / 19.4; FP64 40^3 30.9 / 14.3 / 16.9 / - / 16.3, 48x40x44 - /
+// 20.2 / 17.4 / - / 16.4, 64^3 33.8 / 34.5 / 32.3 / - / 20.9; three at once on streams FP32 40^3 11.1 / 4.5 / 5.0 /
+// 6.4 / 6.0, 48^3 11.2 / 6.3 / 6.1 / 6.1 / 6.0, 64^3 12.0 / 13.3 / 12.2 / 7.8 / 7.6). Element-wise loads
+// (walls) take the 8x8x8 bricks' lead (FP32, walls on x and z, 48^3 14.9 / 9.1, single stages 14.8 / 6.2).
+// FP64 marches start at default_stage_variant's line (128^3 alone / three at once: fused 83.2 / 81.2, per stage
+// 93.1 / 97.6; 112^3 73.2 / 68.7, 80.4 / 51.4, bricks of one stage 59.6 / 51.9).
 int auto_step_variant(int nx, int ny, int nz, int dtype, int scheme, bool walls)
 {
     if (nz == 1) return scheme == PF_EULER ? -1 : variant_by_name(dtype, "fused_plane");
     const int stage = stage_brick_variant(nx, ny, nz, dtype);
     if (scheme == PF_EULER || scheme == PF_RK3) return stage;
-    auto bricks = [&](int bx, int by, int bz) {
-        return (long long)((nx + bx - 1) / bx) * ((ny + by - 1) / by) * ((nz + bz - 1) / bz);
-    };
-    if (bricks(8, 8, 4) <= 256) return variant_by_name(dtype, "fused_brick8x8x4");
+    const long long cus = device_compute_units();
+    if (bricks_of(nx, ny, nz, 8, 8, 4) <= cus) return variant_by_name(dtype, "fused_brick8x8x4");
     if (dtype != PF_F32) return stage;
-    if (bricks(8, 8, 8) <= 256) return variant_by_name(dtype, "fused_brick8x8x8");
-    if (!walls && nx % 4 == 0 && bricks(16, 8, 8) <= 320) return variant_by_name(dtype, "fused_brick16x8x8");
-    const long long cells = (long long)nx * ny * nz, n = walls ? 128 : 108;
-    if (cells <= n * n * n || field_needs_big(nx, ny, nz, 4)) return stage;
+    if (!walls && bricks_of(nx, ny, nz, 8, 8, 8) <= cus) return variant_by_name(dtype, "fused_brick8x8x8");
+    const long long cells = (long long)nx * ny * nz;
+    const long long from = walls ? kWalledFusedMinCellsF32 : kFusedTileMinCellsF32;
+    if (cus <= 0 || cells < from || field_needs_big(nx, ny, nz, 4)) return stage;
     // FP32 marches: the tile whose columns and z-chunks cover the grid in fewer iterations on two
     // workgroups per compute unit (us per step, 32x16 / 64x8, and their iterations: 250x200x150 157 / 132,
     // 45 / 37; 160^3 76.9 / 90.9, 23 / 27; 151x173x129 79.6 / 93.9, 22 / 26). On a tie 64x8 from 256^3
     // cells (275 / 266 us; 512^3 2081 / 1920), 32x16 below and with walls (256^3 354 / 367).
-    const long long slots = 2LL * device_compute_units();
-    if (slots <= 0) return -1;
     auto iterations = [&](int tx, int ty) {
         long long c = 0;
-        (void)march_chunk_planes((long long)((nx + tx - 1) / tx) * ((ny + ty - 1) / ty), nz, slots, 5, 1, &c);
+        (void)march_chunk_planes((long long)((nx + tx - 1) / tx) * ((ny + ty - 1) / ty), nz, 2 * cus, 5, 1, &c);
         return c;
     };
     const long long c64 = iterations(64, 8), c32 = iterations(32, 16);
