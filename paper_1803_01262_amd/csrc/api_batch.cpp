@@ -105,14 +105,19 @@ static bool B_mode_fused(const pf_params* per_instance, int count)
     return cells >= kFusedMinCellsF64;
 }
 
+// Iterations of a tile list: of the workgroup slot that takes longest, and of all its tiles.
+struct PackCost {
+    long long longest, total;
+};
+
 // The global tile list for z-chunks of at most kz planes (an instance's chunks are as even as its
-// planes allow), and the iterations its longest XCD takes. A group of tiles, one chunk of an
-// instance, shares halos in x and y: groups (of at most one XCD's resident workgroups each) are
-// packed onto the 8 XCDs by longest processing time, so their halos meet in one L2. Within an XCD's
-// range the tiles run longest first, so short tiles fill the end; the ranges are padded to one length
-// with empty entries (the launch maps workgroup ids onto the ranges).
-static long long pack_tiles(const pf_params* p, int count, int shape, int slots, int kz,
-                            std::vector<BatchTile>* out)
+// planes allow), and its iterations. A group of tiles, one chunk of an instance, shares halos in x and y:
+// groups (of at most one XCD's resident workgroups each) are packed onto the 8 XCDs by longest processing
+// time, so their halos meet in one L2. Within an XCD's range the tiles run longest first, so short tiles
+// fill the end; the ranges are padded to one length with empty entries (the launch maps workgroup ids onto
+// the ranges).
+static PackCost pack_tiles(const pf_params* p, int count, int shape, int slots, int kz,
+                           std::vector<BatchTile>* out)
 {
     int TX, TY;
     batch_tile_shape(shape, &TX, &TY);
@@ -144,7 +149,8 @@ static long long pack_tiles(const pf_params* p, int count, int shape, int slots,
         num[x] += g.tiles;
         bins[x].push_back(g);
     }
-    long long longest = 0;
+    long long longest = 0, total = 0;
+    for (long long l : load) total += l;
     for (auto& bin : bins) {
         std::stable_sort(bin.begin(), bin.end(), [](const Group& u, const Group& v) { return u.planes > v.planes; });
         // the dispatcher hands the next tile to the workgroup slot that is free first
@@ -159,7 +165,7 @@ static long long pack_tiles(const pf_params* p, int count, int shape, int slots,
     }
     if (out) {
         for (size_t n : num) len = std::max(len, n);
-        if (len * kXcd > 0x7fffffffull) return -1;
+        if (len * kXcd > 0x7fffffffull) return {-1, total};
         out->assign(len * kXcd, BatchTile{-1, 0, 0, 0, 0});
         for (int x = 0; x < kXcd; ++x) {
             BatchTile* t = out->data() + x * len;
@@ -170,13 +176,18 @@ static long long pack_tiles(const pf_params* p, int count, int shape, int slots,
             }
         }
     }
-    return longest;
+    return {longest, total};
 }
 
-// The tile list of a batch: the chunk length whose longest XCD finishes first. Long chunks repeat
-// less warm-up, short ones fill the device and even out the XCDs: 64 planes, whatever the batch,
-// left 40 instances of 32^3-128^3 (29.8 Mcells) at 5.38 ms per 8 FP32 RK4 steps, the choice here
-// (48) takes 4.90; 12 FP64 instances of 32^3-96^3 2.62 / 1.18 ms, 8 of 16^3-32^3 1.06 / 0.42. Ties go to the longer chunk; lists of more than 20000 64-plane tiles take 64 planes.
+// The tile list of a batch. Long chunks repeat less warm-up, short ones fill the device and even out the
+// XCDs, and which counts more depends on what else runs: a batch that has the device to itself takes its
+// longest slot's iterations, one of three at once on streams a third of that or, once the device is full,
+// its share of the total (us per 8 RK4 steps alone / of three, 64-plane chunks and others: 41 FP32 instances
+// of 16^3-121^3 (12.7 Mcells) 2680 / 1778, 32 planes 2060 / 1861, 16 planes 2214 / 2076; 47 FP64 of 16^3-92^3
+// (5.0 M) 2089 / 1545, 16 planes 1978 / 1956; 26 FP32 (1.8 M) 1457 / 532, 12 planes 465 / 326). So the chunk
+// length of the least product of the two, among those that cost one of three at most 8 % over 64 planes by
+// this count (measured: up to 5 %). Ties go to the longer chunk; lists of more than 20000 64-plane tiles take
+// 64 planes.
 static pf_status build_tile_list(const pf_params* p, int count, int shape, std::vector<BatchTile>& out)
 {
     bool walls = false;
@@ -191,16 +202,19 @@ static pf_status build_tile_list(const pf_params* p, int count, int shape, std::
     if (slots <= 0) return fail(PF_ERR_DEVICE, "no device to size the batch for");
     int best_kz = 64;
     if (columns <= 20000) {
-        long long best = -1;
+        auto of_three = [&](const PackCost& c) { return std::max(8LL * slots * c.longest, 3 * c.total); };
+        const long long limit = of_three(pack_tiles(p, count, shape, slots, 64, nullptr));
+        double best = -1.0;
         for (int kz : {128, 96, 64, 48, 32, 24, 16, 12, 8}) {
-            const long long t = pack_tiles(p, count, shape, slots, kz, nullptr);
-            if (best < 0 || t < best) {
-                best = t;
+            const PackCost c = pack_tiles(p, count, shape, slots, kz, nullptr);
+            const double cost = (double)c.longest * (double)of_three(c);
+            if (100.0 * (double)of_three(c) <= 108.0 * (double)limit && (best < 0.0 || cost < best)) {
+                best = cost;
                 best_kz = kz;
             }
         }
     }
-    if (pack_tiles(p, count, shape, slots, best_kz, &out) < 0)
+    if (pack_tiles(p, count, shape, slots, best_kz, &out).longest < 0)
         return fail(PF_ERR_INVALID, "the batch has too many tiles for one launch");
     return PF_OK;
 }
