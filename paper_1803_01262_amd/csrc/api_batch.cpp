@@ -186,9 +186,11 @@ static PackCost pack_tiles(const pf_params* p, int count, int shape, int slots, 
 // of 16^3-121^3 (12.7 Mcells) 2680 / 1778, 32 planes 2060 / 1861, 16 planes 2214 / 2076; 47 FP64 of 16^3-92^3
 // (5.0 M) 2089 / 1545, 16 planes 1978 / 1956; 26 FP32 (1.8 M) 1457 / 532, 12 planes 465 / 326). So the chunk
 // length of the least product of the two, among those that cost one of three at most 8 % over 64 planes by
-// this count (measured: up to 5 %). Ties go to the longer chunk; lists of more than 20000 64-plane tiles take
-// 64 planes.
-static pf_status build_tile_list(const pf_params* p, int count, int shape, std::vector<BatchTile>& out)
+// this count (measured: up to 5 %). Per-stage sweeps are bound by memory, which warm-up planes hardly use
+// (39 FP64 instances, 3.4 M: 64 planes 2372 / 1477, 24 planes 1283 / 1371, 16 planes 1536 / 1370): the longest
+// slot alone decides. Ties go to the longer chunk; lists of more than 20000 64-plane tiles take 64 planes.
+static pf_status build_tile_list(const pf_params* p, int count, int shape, std::vector<BatchTile>& out,
+                                 long long* longest = nullptr)
 {
     bool walls = false;
     long long columns = 0;
@@ -202,7 +204,9 @@ static pf_status build_tile_list(const pf_params* p, int count, int shape, std::
     if (slots <= 0) return fail(PF_ERR_DEVICE, "no device to size the batch for");
     int best_kz = 64;
     if (columns <= 20000) {
-        auto of_three = [&](const PackCost& c) { return std::max(8LL * slots * c.longest, 3 * c.total); };
+        auto of_three = [&](const PackCost& c) -> long long {
+            return shape == kBatchStage32x8 ? 1 : std::max(8 * slots * c.longest, 3 * c.total);
+        };
         const long long limit = of_three(pack_tiles(p, count, shape, slots, 64, nullptr));
         double best = -1.0;
         for (int kz : {128, 96, 64, 48, 32, 24, 16, 12, 8}) {
