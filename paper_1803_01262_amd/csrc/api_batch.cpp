@@ -84,25 +84,38 @@ static int B_stage_only(const pf_params* per_instance, int count)
     return 0;
 }
 
-// Mode: the kind (fused or per-stage) of the variant named by instance 0, else fused, but per-stage for
-// FP64 with walls (a walled 208 x 144 x 176 step takes 292 us in FP64 fused sweeps, 228 per stage)
-// and for FP64 batches that do not fill the device with fused tiles, one to a compute unit. us per 8
-// RK4 steps, fused / per-stage, by total cells: 0.08 M 462 / 422, 3.6 M 1347 / 1179, 5.9 M 2419 / 2479,
-// 8.4 M 2016 / 3296, 11.4 M 3654 / 4940, 29.8 M 8658 / 11935.
+// Mode: the kind (fused or per-stage) of the variant named by instance 0, else fused, but for FP64 per-stage
+// with walls (a walled 208 x 144 x 176 step takes 292 us in FP64 fused sweeps, 228 per stage), where the
+// fused tiles, one to a compute unit, do not fill the device (us per 8 RK4 steps, fused / per-stage, by total
+// cells: 0.08 M 462 / 422, 3.6 M 1347 / 1179, 5.9 M 2419 / 2479, 8.4 M 2016 / 3296, 29.8 M 8658 / 11935), and by
+// B_fused_too_long.
 constexpr long long kFusedMinCellsF64 = 1ll << 22;
 // Per-stage whenever the fused shapes do not apply (B_stage_only).
-static bool B_mode_fused(const pf_params* per_instance, int count)
+static bool B_mode_named(const pf_params* per_instance)
 {
-    if (B_stage_only(per_instance, count)) return false;
-    const int dtype = per_instance[0].dtype, v0 = per_instance[0].variant;
-    if (v0 >= 0 && v0 < stage_variant_count(dtype)) return variant_is_fused(dtype, v0);
-    if (dtype == PF_F32) return true;
-    long long cells = 0;
+    return per_instance[0].variant >= 0 && per_instance[0].variant < stage_variant_count(per_instance[0].dtype);
+}
+static bool B_mode_fused(const pf_params* per_instance, int count, long long* cells)
+{
+    *cells = 0;
+    bool walls = false;
     for (int b = 0; b < count; ++b) {
-        if (wall_mask(per_instance[b])) return false;
-        cells += (long long)per_instance[b].n[0] * per_instance[b].n[1] * per_instance[b].n[2];
+        walls = walls || wall_mask(per_instance[b]) != 0;
+        *cells += (long long)per_instance[b].n[0] * per_instance[b].n[1] * per_instance[b].n[2];
     }
-    return cells >= kFusedMinCellsF64;
+    if (B_stage_only(per_instance, count)) return false;
+    if (B_mode_named(per_instance)) return variant_is_fused(per_instance[0].dtype, per_instance[0].variant);
+    return per_instance[0].dtype == PF_F32 || (!walls && *cells >= kFusedMinCellsF64);
+}
+// FP64 batches whose fused tiles are mostly padding and warm-up, or end in a nearly empty round, run
+// per-stage: those sweeps take what 28 words of a cell take, fused ones what the iterations of the longest
+// slot do. us per 8 RK4 steps alone / one of three at once on streams, fused and per-stage, 4.3-5 M cells each,
+// by those iterations per million cells: planes of 64^2 (53) 9926 / 9569, 4852 / 5122; 100 x 36 x 8 (23) 3614 /
+// 3312, 1920 / 2178; 24^3 (17) 2504 / 2110, 1607 / 1824; 130 of 32^3 (16) 2033 / 1150, 1622 / 1610; 17 of 64^3
+// (14) 1844 / 1143, 1465 / 1662; 40 of 48^3 (12) 1459 / 1386, 1682 / 1761.
+static bool B_fused_too_long(const pf_params* per_instance, long long cells, long long longest)
+{
+    return per_instance[0].dtype == PF_F64 && !B_mode_named(per_instance) && longest * 1000000 > 15 * cells;
 }
 
 // Iterations of a tile list: of the workgroup slot that takes longest, and of all its tiles.
@@ -218,8 +231,9 @@ static pf_status build_tile_list(const pf_params* p, int count, int shape, std::
             }
         }
     }
-    if (pack_tiles(p, count, shape, slots, best_kz, &out).longest < 0)
-        return fail(PF_ERR_INVALID, "the batch has too many tiles for one launch");
+    const PackCost c = pack_tiles(p, count, shape, slots, best_kz, &out);
+    if (c.longest < 0) return fail(PF_ERR_INVALID, "the batch has too many tiles for one launch");
+    if (longest) *longest = c.longest;
     return PF_OK;
 }
 
@@ -244,8 +258,13 @@ extern "C" pf_status phasefield_batch_create(const pf_params* per_instance, int3
                         "instance %d: a field of 4 GiB or more; use a single-grid solver", b);
     }
     std::vector<BatchTile> list;
-    const int shape = B_mode_fused(per_instance, count) ? kBatchFused32x16 : kBatchStage32x8;
-    const pf_status ls = build_tile_list(per_instance, count, shape, list);
+    long long cells = 0, longest = 0;
+    int shape = B_mode_fused(per_instance, count, &cells) ? kBatchFused32x16 : kBatchStage32x8;
+    pf_status ls = build_tile_list(per_instance, count, shape, list, &longest);
+    if (ls == PF_OK && shape == kBatchFused32x16 && B_fused_too_long(per_instance, cells, longest)) {
+        shape = kBatchStage32x8;
+        ls = build_tile_list(per_instance, count, shape, list);
+    }
     if (ls != PF_OK) return ls;
     auto* B = new pf_batch();
     B->count = count;
