@@ -230,6 +230,12 @@ int pf::single_stage_variant(const pf_params& p, int variant)
     return v >= 0 ? v : variant;
 }
 
+bool pf::sweeps_take(const pf_params& p, int variant)
+{
+    return variant_is_fused(p.dtype, variant) &&
+           !(wall_mask(p) != 0 && field_needs_big(p.n[0], p.n[1], p.n[2], p.dtype == PF_F32 ? 4 : 8));
+}
+
 static void store_tuned(int dtype, const int32_t n[3], int v)
 {
     std::lock_guard<std::mutex> lk(g_tune_mu);
@@ -690,9 +696,7 @@ hipError_t pf::enqueue_steps(const pf_params& p, int variant, T* phi, const T* U
     constexpr int dtype = sizeof(T) == 4 ? PF_F32 : PF_F64;
     // the fused sweeps run RK4 and RK2 on uniform meshes with periodic or walled axes (arrays
     // below 4 GiB when walled); otherwise their variants run the per-stage kernel
-    const int wm = wall_mask(p);
-    const bool fused = (p.scheme == PF_RK4 || p.scheme == PF_RK2) && variant_is_fused(dtype, variant) &&
-                       !(wm != 0 && field_needs_big(p.n[0], p.n[1], p.n[2], sizeof(T))) &&
+    const bool fused = (p.scheme == PF_RK4 || p.scheme == PF_RK2) && sweeps_take(p, variant) &&
                        !(nu && nu->on());
     // one-plane grids of a variant that runs a whole step per launch: phi and acc alternate
     const bool plane = p.n[2] == 1 && stage_variant(dtype, variant).plane && p.scheme != PF_EULER &&
@@ -888,7 +892,7 @@ static hipError_t step_stages_impl(pf_solver* s, const T* phi, T* phi_next, cons
     const long long cells = (long long)p.n[0] * p.n[1] * p.n[2];
     const int sv = s->step_variant;
     const bool brick = stage_variant(p.dtype, sv).brick;  // walls too; one plane: single stages
-    const bool fused = !nu && variant_is_fused(p.dtype, sv) && (brick ? p.n[2] > 1 : wall_mask(p) == 0) &&
+    const bool fused = !nu && sweeps_take(p, sv) && (brick ? p.n[2] > 1 : wall_mask(p) == 0) &&
                        (p.dtype == PF_F32 || brick || cells >= 176LL * 176 * 176);
     if (fused && phi_next != phi) {
         // out of place: the two sweeps of the step, the accumulator in phi_next (sweep B writes

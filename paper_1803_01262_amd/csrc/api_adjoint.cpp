@@ -212,7 +212,7 @@ static pf_status adjoint_impl(pf_solver* s, const T* phi, const T* U, const T* V
     // per-stage launches.
     const int sv = s->step_variant;
     // (two-stage bricks take walls; a grid whose steps run single stages recomputes with them)
-    const bool fused_rc = !nu && variant_is_fused(p.dtype, sv) &&
+    const bool fused_rc = !nu && sweeps_take(p, sv) &&
                           (stage_variant(p.dtype, sv).brick ? p.n[2] > 1 : wall_mask(p) == 0);
     const int vs = s->stage_variant != v || fused_rc || !variant_is_fused(p.dtype, v)
                        ? s->stage_variant

@@ -54,6 +54,9 @@ int default_variant(const pf_params& p);  // variant -1: walled grids by rule, e
 // variant where the caller or the tuning cache named it, else bricks on small grids.
 int step_variant(const pf_params& p, int variant);
 int single_stage_variant(const pf_params& p, int variant);
+// Whether the two-stage sweeps of a (fused) variant take the grid: walled arrays of 4 GiB or more run
+// single stages, for steps, kept stages and the adjoint's recompute alike.
+bool sweeps_take(const pf_params& p, int variant);
 void release_graph(StepGraph& g);
 double time_factor(const pf_params& p, double t);
 
