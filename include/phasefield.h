@@ -264,7 +264,8 @@ pf_status phasefield_velocity_coeffs_grad(const pf_params *p, int32_t modes,
  * cell), the column tile (x by y) and, when it ends in a third number, the planes per z-chunk;
  * without one, each launch chooses the chunk length for the grid and the device's resident
  * workgroups. "fused_brick" variants run two stages per launch on bricks (x by y by z) without a
- * march; "fused_plane" a whole step per launch on one-plane grids (bricks on thicker ones). "_big" forces the addressing form of arrays of 4 GiB or more. */
+ * march, "tiled_brick" ones one; "fused_plane" a whole step per launch on one-plane grids (8x8x4 bricks
+ * on thicker ones). "_big" forces the addressing form of arrays of 4 GiB or more. */
 int32_t phasefield_variant_count(int32_t dtype);
 
 /* Short name of a variant (static string), or NULL if out of range. */
@@ -276,18 +277,28 @@ const char *phasefield_variant_name(int32_t dtype, int32_t variant);
  * Synchronises. The choice for a periodic grid is cached per (dtype, grid shape) for the life
  * of the process and used by later phasefield_create calls with variant -1; if the environment
  * variable PF_TUNE_CACHE names a file, the cache is also read from and written to it (one line
- * per entry: dtype nx ny nz variant-name). Without a cached choice, create picks a default from
- * the grid size and dtype (fused sweeps from about 104^3 cells in FP32 and 128^3 in FP64,
- * per-stage kernels below and on every grid of one plane; both with per-launch chunk
- * lengths; whole steps of small and one-plane grids as phasefield_solver_variant says); a grid with walls takes the per-stage kernel in FP64 and, in FP32, the fused 32x16
- * sweeps from about 144^3 cells (per-stage below). */
+ * per entry: dtype nx ny nz variant-name). A fused choice is one of whole steps: single stages and
+ * reverse stages then go by the same rules as on an untuned handle. Without a cached choice, create
+ * picks a default from the grid size and dtype (fused sweeps from about 104^3 cells in FP32 and 128^3
+ * in FP64, per-stage kernels below and on every grid of one plane; both with per-launch chunk
+ * lengths); a grid with walls takes the per-stage kernel in FP64 and, in FP32, the fused 32x16
+ * sweeps from about 144^3 cells (per-stage below). On a grid that is not small (up to 11 bricks of
+ * 16x8x4 cells per compute unit: 104^3 on a whole MI355X) that default is what steps run, but for the
+ * FP32 tile (phasefield_solver_variant). */
 pf_status phasefield_autotune(pf_solver *s, int32_t reps, int32_t *best, double *times_ms,
                               void *hip_stream);
 
-/* The variant a handle runs: its stage kernel, and whole steps too, except that a handle created
- * with variant -1 (and no tuned choice for its grid) runs whole steps of small grids in bricks
- * (RK4, RK2) and of one-plane grids in one launch each (RK4, RK3, RK2), with identical results. */
+/* The variant of a handle: the one named, tuned, or the grid's default. Where neither the caller nor
+ * tuning named one, steps and stages may run others that are faster there, with identical results
+ * (phasefield_solver_routes says which): bricks on small grids and whole steps on one-plane grids, and
+ * in FP32 the fused tile that covers the grid and the device in fewer iterations. */
 int32_t phasefield_solver_variant(const pf_solver *s);
+
+/* What a handle runs: *step the variant of a whole step of its scheme, *stage that of single stages (the
+ * stages a step keeps, the adjoint's recompute), *reverse_bricks 1 if single reverse stages run on bricks
+ * (HOST pointers, any may be NULL). Errors: PF_ERR_INVALID (s NULL). */
+pf_status phasefield_solver_routes(const pf_solver *s, int32_t *step, int32_t *stage,
+                                   int32_t *reverse_bricks);
 
 /* ----------------------------------------------------------------------------------------
  * Batched driver: many independent simulations (each its own pf_params, uneven grid sizes,
@@ -296,11 +307,11 @@ int32_t phasefield_solver_variant(const pf_solver *s);
  * two-stage sweeps per step, or four single-stage sweeps; for RK3, RK2 and Euler one
  * single-stage sweep per stage (Euler then one batched copy of the accumulator into phi).
  * per_instance[0].variant selects the RK4 mode by its kind (a "fused_*" variant or a per-stage
- * one); with variant -1, FP32 runs fused, FP64 too from about 4 M cells in all without walls, else
- * per-stage. Instances may have walls on any axes (each its own), in either mode; a scheme other than RK4 puts the batch in per-stage mode
- * (the fused sweeps pair RK4's stages).
- * The step sequence
- * is replayed from a captured HIP graph. Results are bit-identical to running each instance
+ * one); with variant -1, FP32 runs fused, FP64 too from about 4 M cells in all without walls unless
+ * the grids are small, thin or of one plane (fused tiles mostly padding and warm-up), else per-stage.
+ * Instances may have walls on any axes (each its own), in either mode; a scheme other than RK4 puts
+ * the batch in per-stage mode (the fused sweeps pair RK4's stages). The z-chunks of the tile list weigh
+ * a batch alone on the device against one of three at once on streams. The step sequence is replayed from a captured HIP graph. Results are bit-identical to running each instance
  * alone with phasefield_step.
  * ------------------------------------------------------------------------------------- */
 typedef struct pf_batch pf_batch;

@@ -22,7 +22,7 @@ from ._capi import (EXPORTED, PF_BC_PERIODIC, PF_BC_WALL, PF_ERR_DEVICE, PF_ERR_
                     phasefield_check_params, phasefield_create,
                     phasefield_default_params, phasefield_destroy, phasefield_last_error,
                     phasefield_reduce, phasefield_set_adjoint_form, phasefield_set_spacing,
-                    phasefield_solver_variant, phasefield_step, phasefield_step_stages,
+                    phasefield_solver_routes, phasefield_solver_variant, phasefield_step, phasefield_step_stages,
                     phasefield_adjoint_step_stages,
                     phasefield_step_noalloc, phasefield_noalloc_scratch_bytes, phasefield_device_copy,
                     phasefield_variant_count, phasefield_variant_name,
@@ -112,6 +112,14 @@ class Solver:
     @property
     def variant_name(self) -> str:
         return phasefield_variant_name(self.params.dtype, self.variant)
+
+    @property
+    def routes(self):
+        """Names of the variants that whole steps and single stages run, and whether reverse stages
+        run on bricks."""
+        step, stage, bricks = phasefield_solver_routes(self.handle)
+        return (phasefield_variant_name(self.params.dtype, step),
+                phasefield_variant_name(self.params.dtype, stage), bricks)
 
     def report(self, max_face_speed: float) -> Report:
         return phasefield_check_params(self.params, max_face_speed)

@@ -86,6 +86,7 @@ def _load():
         "phasefield_variant_name": (ctypes.c_char_p, [i32, i32]),
         "phasefield_autotune": (i32, [vp, i32, P(i32), P(d), vp]),
         "phasefield_solver_variant": (i32, [vp]),
+        "phasefield_solver_routes": (i32, [vp, P(i32), P(i32), P(i32)]),
         "phasefield_set_adjoint_form": (i32, [vp, i32]),
         "phasefield_set_spacing": (i32, [vp, vp, vp, vp, i32]),
         "phasefield_batch_create": (i32, [P(Params), i32, P(vp)]),
@@ -114,7 +115,7 @@ EXPORTED = ("phasefield_default_params", "phasefield_check_params", "phasefield_
             "phasefield_reduce", "phasefield_velocity_from_coeffs",
             "phasefield_velocity_coeffs_grad", "phasefield_variant_count",
             "phasefield_variant_name", "phasefield_autotune", "phasefield_solver_variant",
-            "phasefield_set_adjoint_form", "phasefield_set_spacing",
+            "phasefield_solver_routes", "phasefield_set_adjoint_form", "phasefield_set_spacing",
             "phasefield_batch_create", "phasefield_batch_step", "phasefield_batch_destroy",
             "phasefield_batch_set_persistent", "phasefield_batch_set_shape",
             "phasefield_batch_autotune",
@@ -300,6 +301,13 @@ def phasefield_autotune(h, reps=5, stream=None, dtype=PF_F64):
 
 def phasefield_solver_variant(h) -> int:
     return int(lib.phasefield_solver_variant(h))
+
+
+def phasefield_solver_routes(h):
+    """(variant of whole steps, variant of single stages, whether reverse stages run on bricks)."""
+    out = [ctypes.c_int32() for _ in range(3)]
+    _check(lib.phasefield_solver_routes(h, *[ctypes.byref(o) for o in out]))
+    return out[0].value, out[1].value, bool(out[2].value)
 
 
 def phasefield_batch_create(params_list) -> ctypes.c_void_p:

@@ -216,18 +216,38 @@ static bool variant_named(const pf_params& p)
     return g_tuned.count(std::make_tuple(p.dtype, p.n[0], p.n[1], p.n[2])) != 0;
 }
 
-int pf::step_variant(const pf_params& p, int variant)
+bool pf::stages_by_rule(const pf_params& p, int variant, bool tuned)
 {
-    if (variant_named(p)) return variant;
-    const int v = auto_step_variant(p.n[0], p.n[1], p.n[2], p.dtype, p.scheme, wall_mask(p) != 0);
+    if (!tuned && !variant_named(p)) return true;
+    if (stage_variant(p.dtype, variant).brick) return true;
+    return (tuned || p.variant < 0) && variant_is_fused(p.dtype, variant);
+}
+
+int pf::single_stage_variant(const pf_params& p, int variant, bool by_rule)
+{
+    const int v = by_rule ? stage_brick_variant(p.n[0], p.n[1], p.n[2], p.dtype) : -1;
     return v >= 0 ? v : variant;
 }
 
-int pf::single_stage_variant(const pf_params& p, int variant)
+int pf::step_variant(const pf_params& p, int variant, bool tuned)
 {
-    if (variant_named(p)) return variant;
-    const int v = stage_brick_variant(p.n[0], p.n[1], p.n[2], p.dtype);
-    return v >= 0 ? v : variant;
+    int v = variant;
+    if (!tuned && !variant_named(p)) {
+        const int a = auto_step_variant(p.n[0], p.n[1], p.n[2], p.dtype, p.scheme, wall_mask(p) != 0);
+        if (a >= 0) v = a;
+    }
+    // Euler and RK3 steps are single stages, but for RK3 on one plane
+    const bool plane = p.n[2] == 1 && stage_variant(p.dtype, v).plane && p.scheme == PF_RK3;
+    if ((p.scheme == PF_EULER || p.scheme == PF_RK3) && variant_is_fused(p.dtype, v) && !plane)
+        v = single_stage_variant(p, v, stages_by_rule(p, variant, tuned));
+    return v;
+}
+
+bool pf::reverse_on_bricks(const pf_solver& s)
+{
+    const pf_params& p = s.p;
+    return s.stages_by_rule && !s.nu.on() && adjoint_takes_bricks(p.n[0], p.n[1], p.n[2]) &&
+           !field_needs_big(p.n[0], p.n[1], p.n[2], s.esz);
 }
 
 bool pf::sweeps_take(const pf_params& p, int variant)
@@ -283,7 +303,8 @@ extern "C" pf_status phasefield_create(const pf_params* p, pf_solver** out)
     s->esz = p->dtype == PF_F32 ? sizeof(float) : sizeof(double);
     s->variant = p->variant >= 0 ? p->variant : default_variant(*p);
     s->step_variant = step_variant(*p, s->variant);
-    s->stage_variant = single_stage_variant(*p, s->variant);
+    s->stages_by_rule = stages_by_rule(*p, s->variant, false);
+    s->stage_variant = single_stage_variant(*p, s->variant, s->stages_by_rule);
     hipError_t e = hipSuccess;
     for (void** b : {&s->ya, &s->yb, &s->acc}) {
         e = hipMalloc(b, s->N * s->esz);
@@ -405,6 +426,27 @@ extern "C" pf_status phasefield_set_spacing(pf_solver* s, const double* hx, cons
 }
 
 extern "C" int32_t phasefield_solver_variant(const pf_solver* s) { return s ? s->variant : -1; }
+
+extern "C" pf_status phasefield_solver_routes(const pf_solver* s, int32_t* step, int32_t* stage,
+                                              int32_t* reverse_bricks)
+{
+    if (!s) return fail(PF_ERR_INVALID, "solver is NULL");
+    const pf_params& p = s->p;
+    auto single = [&](int v) {  // the variant of a single stage
+        const bool bricks = stage_variant(p.dtype, v).brick && !variant_is_fused(p.dtype, v);
+        if (s->nu.on() && !(bricks && stage_takes_bricks(p.n[0], p.n[1], p.n[2], p.dtype, true)))
+            return per_stage_variant(p.n[0], p.n[1], p.n[2], p.dtype);
+        return variant_is_fused(p.dtype, v) ? per_stage_variant(p.n[0], p.n[1], p.n[2], p.dtype) : v;
+    };
+    const int v = s->step_variant;
+    const bool whole = !s->nu.on() && (stage_variant(p.dtype, v).plane && p.n[2] == 1
+                                           ? p.scheme != PF_EULER
+                                           : (p.scheme == PF_RK4 || p.scheme == PF_RK2) && sweeps_take(p, v));
+    if (step) *step = whole ? v : single(v);
+    if (stage) *stage = single(s->stage_variant);
+    if (reverse_bricks) *reverse_bricks = reverse_on_bricks(*s) ? 1 : 0;
+    return PF_OK;
+}
 
 pf_status pf::check_field_ptr(const void* ptr, const char* name)
 {
@@ -1036,7 +1078,13 @@ static pf_status autotune_impl(pf_solver* s, int reps, int32_t* best, double* ti
     double best_t = INFINITY;
     int best_v = s->variant;
     const int nv = stage_variant_count(p.dtype);
+    const int brick = stage_variant_index(p.dtype, "fused_brick8x8x4");
+    double brick_t = INFINITY;
     for (int v = 0; v < nv && e == hipSuccess; ++v) {
+        if (stage_variant(p.dtype, v).plane && p.n[2] > 1) {  // the 8x8x4 bricks under a second name
+            if (times_ms) times_ms[v] = brick_t;
+            continue;
+        }
         e = enqueue_steps<T>(p, v, phi, U, V, W, (T*)s->ya, (T*)s->yb, (T*)s->acc, 0.0, 2, st);
         if (e != hipSuccess) break;
         e = hipEventRecord(ev0, st);
@@ -1049,6 +1097,7 @@ static pf_status autotune_impl(pf_solver* s, int reps, int32_t* best, double* ti
         if (e == hipSuccess) e = hipEventElapsedTime(&ms, ev0, ev1);
         const double per = ms / (2.0 * std::max(reps, 1));
         if (times_ms) times_ms[v] = per;
+        if (v == brick) brick_t = per;
         if (e == hipSuccess && per < best_t) {
             best_t = per;
             best_v = v;
@@ -1061,7 +1110,10 @@ static pf_status autotune_impl(pf_solver* s, int reps, int32_t* best, double* ti
     for (T* b : {phi, U, V, W})
         if (b) (void)hipFree(b);
     if (ret == PF_OK) {
-        s->variant = s->step_variant = s->stage_variant = best_v;
+        s->variant = best_v;
+        s->step_variant = step_variant(p, best_v, true);
+        s->stages_by_rule = stages_by_rule(p, best_v, true);
+        s->stage_variant = single_stage_variant(p, best_v, s->stages_by_rule);
         if (wall_mask(p) == 0) store_tuned(p.dtype, p.n, best_v);  // the cache is for periodic grids
         release_graph(s->graph);
         if (best) *best = best_v;

@@ -131,9 +131,7 @@ static pf_status adjoint_impl(pf_solver* s, const T* phi, const T* U, const T* V
     // a non-uniform mesh: the forward's per-stage NU kernel for the recompute, the NU forms of the
     // plain and tiled adjoint kernels for the reverse stages
     const NuMesh* nu = s->nu.on() ? &s->nu : nullptr;
-    // a handle whose variant was not named runs single reverse stages of small grids on bricks
-    const bool bricks = p.variant < 0 && !nu && adjoint_takes_bricks(p.n[0], p.n[1], p.n[2]) &&
-                        !field_needs_big(p.n[0], p.n[1], p.n[2], sizeof(T));
+    const bool bricks = reverse_on_bricks(*s);
     auto adj = [&](const AdjArgs<T>& a, hipStream_t hs) {
         if (plain) return nu ? launch_adjoint_stage_nu<T>(a, hs) : launch_adjoint_stage_global<T>(a, hs);
         if (bricks) return launch_adjoint_brick<T>(a, hs);

@@ -50,10 +50,16 @@ pf_status check_field_ptr(const void* ptr, const char* name);
 int scheme_stage_count(int scheme);  // stage inputs an RK step keeps for its adjoint
 int tuned_variant(int dtype, const int32_t n[3]);
 int default_variant(const pf_params& p);  // variant -1: walled grids by rule, else tuned_variant
-// The variants that whole steps and single stages of a handle or call of `variant` run: that
-// variant where the caller or the tuning cache named it, else bricks on small grids.
-int step_variant(const pf_params& p, int variant);
-int single_stage_variant(const pf_params& p, int variant);
+// The variant that whole steps of a handle or call of `variant` run: that variant where the caller or the
+// tuning cache named it (tuned: this handle was tuned to it), else by rule (auto_step_variant).
+int step_variant(const pf_params& p, int variant, bool tuned = false);
+// Whether single stages, forward and reverse, go by rule (bricks on small grids): the variant was not named,
+// or is one of bricks itself, or was chosen by tuning (this handle's, or the cache's) and is fused, which
+// says nothing of single stages. Another named or tuned variant runs them itself and lends its tile to the
+// reverse stages.
+bool stages_by_rule(const pf_params& p, int variant, bool tuned);
+int single_stage_variant(const pf_params& p, int variant, bool by_rule);
+bool reverse_on_bricks(const pf_solver& s);
 // Whether the two-stage sweeps of a (fused) variant take the grid: walled arrays of 4 GiB or more run
 // single stages, for steps, kept stages and the adjoint's recompute alike.
 bool sweeps_take(const pf_params& p, int variant);
@@ -97,6 +103,7 @@ struct pf_solver {
     size_t esz = 0;     // bytes per element
     int variant = 0;        // the reported variant; the adjoint's tile
     int step_variant = 0;   // whole steps (step_variant(): bricks on small grids)
+    bool stages_by_rule = true;  // pf::stages_by_rule
     int stage_variant = 0;  // single stages (single_stage_variant())
     int adjoint_form = -1;  // reverse RK4 stages: -1 chosen per grid, 0 one per launch, 1 two
     void* ya = nullptr;  // RK stage buffers
