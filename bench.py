@@ -31,16 +31,19 @@ FP64_PEAK_TFLOPS = 78.6  # dense FP64, MI355X
 # value and accumulator out). The fused two-stage sweeps keep the middle stage value on chip and
 # move 6 + 7 = 13 words, which is reported beside it as the fused minimum.
 ALG_WORDS = 28
-WORDS_PER_CELL_STEP = {"tiled": 28, "global": 28, "fused": 13}
-LAUNCHES_PER_STEP = {"tiled": 4, "global": 4, "fused": 2}
+# A one-plane grid's whole step in one launch reads phi, U, V and W and writes phi.
+WORDS_PER_CELL_STEP = {"tiled": 28, "global": 28, "fused": 13, "plane": 5}
+LAUNCHES_PER_STEP = {"tiled": 4, "global": 4, "fused": 2, "plane": 1}
 GRAPH_STEPS = 8  # steps per captured graph in the library (steady velocity)
 # the explicit midpoint rule: per-stage S1 reads phi, U, V, W and writes ya; S2 reads ya, phi, U,
 # V, W and writes phi. Fused: one sweep reads phi, U, V, W and writes the new phi.
-RK2_WORDS_PER_CELL_STEP = {"tiled": 11, "global": 11, "fused": 5}
+RK2_WORDS_PER_CELL_STEP = {"tiled": 11, "global": 11, "fused": 5, "plane": 5}
 
 
 def kind(variant_name: str) -> str:
-    return variant_name.split("_")[0]
+    return "plane" if variant_name == "fused_plane" else variant_name.split("_")[0]
+
+
 KERNEL_SOURCES = ("paper_1803_01262_amd/csrc/pf_tiled_body.h", "paper_1803_01262_amd/csrc/pf_cell.h",
                   "paper_1803_01262_amd/csrc/stage_tiled.hip", "paper_1803_01262_amd/csrc/pf_fused_body.h",
                   "paper_1803_01262_amd/csrc/pf_fused_launch.h",
@@ -110,7 +113,7 @@ def time_forward(pf, c, phi, u, v, w, dtype, steps, warmup, st, autotune=True, v
         m0 = s.reduce(phi, stream=st)
         ms = cuda_timer(st, lambda: s.step(phi, u, v, w, nsteps=steps, stream=st)) / steps
         m1 = s.reduce(phi, stream=st)
-    name = s.variant_name
+    name = s.routes[0]  # what steps run
     s.close()
     return ms, name, tuned, m0, m1
 
@@ -226,7 +229,7 @@ def deformation_timing(pf, fx, st, dtype, n=256, steps=100):
         phi.copy_(keep)
         del keep
         ms = cuda_timer(st, lambda: s.step(phi, u, v, w, t0=0.0, nsteps=steps, stream=st)) / steps
-    name = s.variant_name
+    name = s.routes[0]  # what steps run
     s.close()
     cells = n ** 3
     e = 8 if dtype == "f64" else 4
@@ -268,7 +271,7 @@ def vortex_timing(pf, fx, st):
         if key == "cos_us_per_step":
             out["e_shape"] = float((phi - phi0).abs().sum()) * c.dx * c.dx
         out[key] = round(1e3 * ms / c.nsteps, 2)
-        out["variant"] = s.variant_name
+        out["variant"] = s.routes[0]
         s.close()
     return out
 
