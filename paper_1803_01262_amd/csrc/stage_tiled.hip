@@ -413,15 +413,19 @@ int auto_step_variant(int nx, int ny, int nz, int dtype, int scheme, bool walls)
     if (cus <= 0 || cells < from || field_needs_big(nx, ny, nz, 4)) return stage;
     // FP32 marches: the tile whose columns and z-chunks cover the grid in fewer iterations on two
     // workgroups per compute unit (us per step, 32x16 / 64x8, and their iterations: 250x200x150 157 / 132,
-    // 45 / 37; 160^3 76.9 / 90.9, 23 / 27; 151x173x129 79.6 / 93.9, 22 / 26). On a tie 64x8 from 256^3
-    // cells (275 / 266 us; 512^3 2081 / 1920), 32x16 below and with walls (256^3 354 / 367).
+    // 45 / 37; 160^3 76.9 / 90.9, 23 / 27; 151x173x129 79.6 / 93.9, 22 / 26). On a tie 64x8 from 256^3 cells
+    // (275 / 266 us; 512^3 2081 / 1920) unless those pad more columns, which a shared device pays for
+    // (263x268x300 RK2, 5 steps, 153 / 170 columns: alone 1549 / 1515 us, of three at once 1448 / 1531); 32x16
+    // below and with walls (256^3 354 / 367).
+    auto columns = [&](int tx, int ty) { return (long long)((nx + tx - 1) / tx) * ((ny + ty - 1) / ty); };
     auto iterations = [&](int tx, int ty) {
         long long c = 0;
-        (void)march_chunk_planes((long long)((nx + tx - 1) / tx) * ((ny + ty - 1) / ty), nz, 2 * cus, 5, 1, &c);
+        (void)march_chunk_planes(columns(tx, ty), nz, 2 * cus, 5, 1, &c);
         return c;
     };
     const long long c64 = iterations(64, 8), c32 = iterations(32, 16);
-    const bool x64 = c64 < c32 || (c64 == c32 && !walls && cells >= kX64MinCellsF32);
+    const bool x64 = c64 < c32 || (c64 == c32 && !walls && cells >= kX64MinCellsF32 &&
+                                   columns(64, 8) <= columns(32, 16));
     return variant_by_name(dtype, x64 ? "fused_64x8" : "fused_32x16");
 }
 

@@ -88,8 +88,9 @@ def test_a_tuned_handle_keeps_its_rules(pf):
 
 
 def test_default_routes_of_larger_grids(pf):
-    """The FP32 tile by the march; stretched meshes and one plane."""
-    for shape, dtype, scheme, want in (((250, 200, 150), "f32", "rk4", "fused_64x8"), ((160, 160, 160), "f32", "rk2", "fused_32x16"),
+    """The FP32 tile by the march, on a tie the one that pads fewer columns; one plane."""
+    for shape, dtype, scheme, want in (((250, 200, 150), "f32", "rk4", "fused_64x8"), ((263, 268, 300), "f32", "rk2", "fused_32x16"),
+                                       ((256, 256, 256), "f32", "rk4", "fused_64x8"), ((160, 160, 160), "f32", "rk2", "fused_32x16"),
                                        ((160, 160, 160), "f32", "rk3", "tiled_32x4"), ((128, 128, 128), "f64", "rk4", "fused_32x16"),
                                        ((64, 64, 1), "f64", "rk3", "fused_plane"), ((64, 64, 1), "f64", "euler", "tiled_32x4")):
         dx = 1.0 / max(shape)
