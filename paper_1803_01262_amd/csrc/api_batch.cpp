@@ -3,7 +3,7 @@
 // step sequence is captured once into a HIP graph and replayed.
 //
 // Two modes. The kind of the variant that instance 0 names (variant >= 0) selects one; with
-// variant -1 FP32 runs fused and FP64 per-stage:
+// variant -1 FP32 runs fused, and FP64 by the rules at B_mode_fused:
 //   fused:     two-stage sweeps (two launches per step). phi alternates with the accumulator
 //              buffer from step to step; tables for even and odd steps are kept, and after an
 //              odd step count one batched copy returns phi to the caller's buffers.

@@ -525,7 +525,9 @@ __device__ __forceinline__ void fused_body(Args& a, int ti, int tj, int k0, int 
             qzn[s] = n_adv[s] = n_dif[s] = n_c[s] = T(0);
             if (s == 1 && !has_ring) continue;
             const int oi = (e_lx[s] + 2) + (e_ly[s] + 2) * INW;
-            if constexpr (R == 0 && !WITH_E2) {  // the march's first iteration: nothing handed down yet
+            // the march's first iteration: nothing handed down yet (the one-barrier march's fifth, which
+            // has this form too, reads the same values again)
+            if constexpr (R == 0 && !WITH_E2) {
                 e_c0[s] = IA[oi];
                 e_c1[s] = IB[oi];
             }

@@ -8,7 +8,7 @@
 // (RK3 20 x 20, RK2 24 x 24). Field, velocities and accumulator of a cell stay in its thread's
 // registers, only the stage value and its sharpening products pass through LDS: one round of loads
 // and two barriers per stage. What bounds it: latency up to about one patch per compute unit
-// (256^2 cells), then the halo cells evaluated again (RK4: a patch evaluates f at 2240 cells
+// (256^2 cells), then the halo cells evaluated again (RK4: a patch evaluates f at 2016 cells
 // for 1024 in the plane's own four evaluations). us per RK4 step from graphs, four launches / this
 // kernel: FP64 64^2 13.1 / 5.8, 256^2 14.9 / 6.4, 512^2 19.0 / 13.9, 1024^2 45.7 / 41.2, 2048^2
 // 153.4 / 152.5, 4096^2 750 / 625; FP32 64^2 12.3 / 4.8, 512^2 16.2 / 10.0, 2048^2 108.3 / 104.3,
