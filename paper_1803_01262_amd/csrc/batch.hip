@@ -38,7 +38,7 @@ __device__ __forceinline__ void for_batch_tiles(const BatchTile* __restrict__ ti
 // An instance's arguments in the constant address space (the tables are written before the launch
 // and never during it), so that the march reads them with scalar loads wherever it needs them: read
 // through an ordinary pointer they are held in vector registers across its barriers and stores, and
-// the FP32 sweep B spilled 12 of them (40 instances of 32^3-128^3: 4.97 / 4.17 ms per 8 steps with / without).
+// the FP32 sweep B spilled 12 of them (40 instances of 32^3-128^3 took 1.19 times as long).
 template <typename A>
 using ConstArgs = const __attribute__((address_space(4))) A;
 template <typename A>

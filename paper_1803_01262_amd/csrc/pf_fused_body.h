@@ -244,7 +244,7 @@ __device__ __forceinline__ void fused_body(Args& a, int ti, int tj, int k0, int 
     }
     // ---- q2 halo cell (threads at the top of the block, which have no ring work). Where no thread
     // has both kinds of halo cell, the two share their registers (with them apart, the batched FP32
-    // sweep B spilled one in its loop: 40 instances of 32^3-128^3, 4.90 -> 4.43 ms per 8 steps)
+    // sweep B spilled one in its loop: 40 instances of 32^3-128^3 took 1.11 times as long)
     constexpr bool ONE_HALO = OUT0 + NOUT <= NT - NH2;
     const int rh = tid - (NT - NH2);
     const bool has_h2 = rh >= 0;
