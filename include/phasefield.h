@@ -282,9 +282,9 @@ const char *phasefield_variant_name(int32_t dtype, int32_t variant);
  * picks a default from the grid size and dtype (fused sweeps from about 104^3 cells in FP32 and 128^3
  * in FP64, per-stage kernels below and on every grid of one plane; both with per-launch chunk
  * lengths); a grid with walls takes the per-stage kernel in FP64 and, in FP32, the fused 32x16
- * sweeps from about 144^3 cells (per-stage below). On a grid that is not small (up to 11 bricks of
- * 16x8x4 cells per compute unit: 104^3 on a whole MI355X) that default is what steps run, but for the
- * FP32 tile (phasefield_solver_variant). */
+ * sweeps from about 144^3 cells (per-stage below). On a grid that is not small (bricks lead up to
+ * about 112^3 cells on a whole MI355X) that default is what steps run, but for the FP32 tile
+ * (phasefield_solver_variant). */
 pf_status phasefield_autotune(pf_solver *s, int32_t reps, int32_t *best, double *times_ms,
                               void *hip_stream);
 

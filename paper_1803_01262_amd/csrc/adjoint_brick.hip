@@ -144,17 +144,17 @@ hipError_t launch_adjoint_brick(const AdjArgs<T>& a, hipStream_t st)
 template hipError_t launch_adjoint_brick<float>(const AdjArgs<float>&, hipStream_t);
 template hipError_t launch_adjoint_brick<double>(const AdjArgs<double>&, hipStream_t);
 
-// Up to 14 bricks of 16x8x4 per compute unit, where neither a grid alone on the device nor one beside
+// Up to 15 bricks of 16x8x4 per compute unit, where neither a grid alone on the device nor one beside
 // others loses more than the other gains (stage_takes_bricks; us per RK4 adjoint step alone / each of three
 // at once on streams, march -> bricks: FP32 64x72x101 (936 bricks) 71.8 / 33.6 -> 46.0 / 28.0, 112x88x116
-// (2233) 124.0 / 70.7 -> 80.4 / 59.8, 128x108x126 (3584) 130.0 / 101.9 -> 108.4 / 112.3, 128^3 (4096) 135.8 / 125.3 ->
-// 123.6 / 152.7; FP64 85.9 / 68.8 -> 63.8 / 45.6, 172.3 / 149.7 -> 118.7 / 143.6, 198.9 / 212.3 -> 180.6 / 232.4,
-// 120x97x145 (3848) 197.9 / 227.3 -> 182.7 / 261.1). One plane: us for the four reverse stages FP64 64^2 35.8 /
+// (2233) 124.0 / 70.7 -> 80.4 / 59.8, 120^3 (3600) 133.6 / 104.3 -> 118.1 / 115.5, 128^3 (4096) 135.8 / 125.3 ->
+// 123.6 / 152.7; FP64 85.9 / 68.8 -> 63.8 / 45.6, 172.3 / 149.7 -> 118.7 / 143.6, 211.5 / 221.4 -> 195.3 / 249.2,
+// 126x120x128 (3840) 205.3 / 251.7 -> 196.0 / 283.0). One plane: us for the four reverse stages FP64 64^2 35.8 /
 // 19.9, 512^2 81 / 47.
 bool adjoint_takes_bricks(int nx, int ny, int nz)
 {
     const long long bricks = (long long)((nx + 15) / 16) * ((ny + 7) / 8) * ((nz + 3) / 4);
-    return nz == 1 || bricks <= 14LL * device_compute_units();
+    return nz == 1 || bricks <= 15LL * device_compute_units();
 }
 
 }  // namespace pf

@@ -225,7 +225,7 @@ bool pf::stages_by_rule(const pf_params& p, int variant, bool tuned)
 
 int pf::single_stage_variant(const pf_params& p, int variant, bool by_rule)
 {
-    const int v = by_rule ? stage_brick_variant(p.n[0], p.n[1], p.n[2], p.dtype) : -1;
+    const int v = by_rule ? stage_brick_variant(p.n[0], p.n[1], p.n[2], p.dtype, wall_mask(p) != 0) : -1;
     return v >= 0 ? v : variant;
 }
 
@@ -434,7 +434,7 @@ extern "C" pf_status phasefield_solver_routes(const pf_solver* s, int32_t* step,
     const pf_params& p = s->p;
     auto single = [&](int v) {  // the variant of a single stage
         const bool bricks = stage_variant(p.dtype, v).brick && !variant_is_fused(p.dtype, v);
-        if (s->nu.on() && !(bricks && stage_takes_bricks(p.n[0], p.n[1], p.n[2], p.dtype, true)))
+        if (s->nu.on() && !(bricks && stage_takes_bricks(p.n[0], p.n[1], p.n[2], p.dtype, true, wall_mask(p) != 0)))
             return per_stage_variant(p.n[0], p.n[1], p.n[2], p.dtype);
         return variant_is_fused(p.dtype, v) ? per_stage_variant(p.n[0], p.n[1], p.n[2], p.dtype) : v;
     };

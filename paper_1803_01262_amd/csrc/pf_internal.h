@@ -241,8 +241,8 @@ int default_stage_variant(int nx, int ny, int nz, int dtype);
 constexpr long long kWalledFusedMinCellsF32 = 144LL * 144 * 144;
 // Whether single stages of a grid run on bricks (handles whose variant was not named), and the
 // brick variant for them (-1: the handle's own).
-bool stage_takes_bricks(int nx, int ny, int nz, int dtype, bool nu);
-int stage_brick_variant(int nx, int ny, int nz, int dtype);
+bool stage_takes_bricks(int nx, int ny, int nz, int dtype, bool nu, bool walls);
+int stage_brick_variant(int nx, int ny, int nz, int dtype, bool walls);
 // The variant for whole steps of a grid (bricks on small ones; FP32 marches on the tile that covers
 // the grid and the device in fewer iterations), or -1: its stage variant's own step.
 int auto_step_variant(int nx, int ny, int nz, int dtype, int scheme, bool walls);

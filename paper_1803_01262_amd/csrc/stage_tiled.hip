@@ -311,7 +311,7 @@ template hipError_t launch_stage_nu_march<double>(const StageArgs<double>&, hipS
 template <typename T>
 hipError_t launch_stage_nu(const StageArgs<T>& a, bool bricks, hipStream_t st)
 {
-    return bricks && stage_takes_bricks(a.nx, a.ny, a.nz, sizeof(T) == 4 ? PF_F32 : PF_F64, true)
+    return bricks && stage_takes_bricks(a.nx, a.ny, a.nz, sizeof(T) == 4 ? PF_F32 : PF_F64, true, a.walls != 0)
                ? launch_stage_brick<T, 16, 8, 4>(a, st)
                : launch_stage_nu_march<T>(a, st);
 }
@@ -368,22 +368,23 @@ static long long bricks_of(int nx, int ny, int nz, int bx, int by, int bz)
 // So the line, in bricks of 16x8x4 per compute unit, lies where neither use loses more than the other
 // gains (MI355X, us per step alone / each of three at once on streams, march -> bricks. RK3 FP32: 80x82x72
 // (990 bricks) 26.4 / 11.8 -> 16.7 / 9.1, 72x104x112 (1820) 33.3 / 17.8 -> 24.6 / 15.6, 112x105x114 (2842)
-// 40.5 / 24.0 -> 33.1 / 23.3, 116x115x108 (3240) 40.7 / 24.2 -> 36.0 / 26.6, 128^3 (4096) 49.9 / 31.4 -> 42.5 /
-// 33.4; FP64, the same grids: 30.8 / 15.4 -> 21.0 / 16.6, 39.7 / 27.4 -> 31.9 / 22.7, 54.9 / 34.1 -> 42.9 / 35.5,
-// 50.9 / 36.5 -> 46.7 / 44.5, 63.6 / 64.7 -> 57.1 / 70.1; RK4 with walls on x and z 104x105x110 (2744) FP32 59.7 /
-// 38.3 -> 46.0 / 38.6, FP64 83.4 / 47.4 -> 58.6 / 49.2). Lower on a non-uniform mesh, whose tables every brick
+// 40.5 / 24.0 -> 33.1 / 23.3, 117^3 (3600) 46.8 / 27.8 -> 39.7 / 29.6, 128^3 (4096) 49.9 / 31.4 -> 42.5 / 33.4;
+// FP64, the same grids: 30.8 / 15.4 -> 21.0 / 16.6, 39.7 / 27.4 -> 31.9 / 22.7, 54.9 / 34.1 -> 42.9 / 35.5, 57.3 / 44.1
+// -> 53.0 / 56.7, 63.6 / 64.7 -> 57.1 / 70.1; RK4 with walls on x and z, whose element-wise loads cost the march
+// more, 104x105x110 (2744) FP32 59.7 / 38.3 -> 46.0 / 38.6, FP64 83.4 / 47.4 -> 58.6 / 49.2, 120x124x119 (3840)
+// 77.5 / 38.0 -> 59.1 / 47.1, 95.5 / 77.7 -> 79.6 / 74.7). Lower on a non-uniform mesh, whose tables every brick
 // reads again (RK4, widest-cell eps, FP32: 74x92x80 (1200) 46.7 / 23.0 -> 32.6 / 20.2, 71x93x118 (1800) 53.4 /
 // 34.1 -> 44.1 / 29.8, 121x89x125 (3072) 72.3 / 34.8 -> 64.3 / 52.1; FP64 54.7 / 39.8 -> 49.4 / 35.9, 81x84x89
 // (1518) 55.8 / 42.2 -> 59.6 / 46.4). One-plane grids have their own kernel.
-bool stage_takes_bricks(int nx, int ny, int nz, int dtype, bool nu)
+bool stage_takes_bricks(int nx, int ny, int nz, int dtype, bool nu, bool walls)
 {
-    const int per_unit = !nu ? 11 : dtype == PF_F32 ? 8 : 5;
+    const int per_unit = nu ? (dtype == PF_F32 ? 8 : 5) : walls ? 15 : dtype == PF_F32 ? 16 : 12;
     return nz > 1 && bricks_of(nx, ny, nz, 16, 8, 4) <= (long long)per_unit * device_compute_units();
 }
 
-int stage_brick_variant(int nx, int ny, int nz, int dtype)
+int stage_brick_variant(int nx, int ny, int nz, int dtype, bool walls)
 {
-    return stage_takes_bricks(nx, ny, nz, dtype, false) ? variant_by_name(dtype, "tiled_brick16x8x4") : -1;
+    return stage_takes_bricks(nx, ny, nz, dtype, false, walls) ? variant_by_name(dtype, "tiled_brick16x8x4") : -1;
 }
 
 // Whole RK4 and RK2 steps of small grids (and RK3 of one-plane grids): a brick variant, or -1 where
@@ -402,7 +403,7 @@ int stage_brick_variant(int nx, int ny, int nz, int dtype)
 int auto_step_variant(int nx, int ny, int nz, int dtype, int scheme, bool walls)
 {
     if (nz == 1) return scheme == PF_EULER ? -1 : variant_by_name(dtype, "fused_plane");
-    const int stage = stage_brick_variant(nx, ny, nz, dtype);
+    const int stage = stage_brick_variant(nx, ny, nz, dtype, walls);
     if (scheme == PF_EULER || scheme == PF_RK3) return stage;
     const long long cus = device_compute_units();
     if (bricks_of(nx, ny, nz, 8, 8, 4) <= cus) return variant_by_name(dtype, "fused_brick8x8x4");

@@ -9,8 +9,8 @@ pytestmark = pytest.mark.gpu
 CASES = [
     # dtype, grid, walls: two-stage bricks end at one per compute unit (256: 64 x 64 x 16 in 8x8x4), ...
     ("f32", (64, 64, 16), ""), ("f32", (64, 64, 17), ""), ("f64", (64, 64, 17), ""),
-    # ... single-stage bricks at 11 (2816: 128 x 128 x 88), walls take the same line
-    ("f64", (128, 128, 88), ""), ("f64", (129, 128, 88), ""), ("f64", (112, 109, 111), "xz"),
+    # ... single-stage bricks at 12 in FP64 (3072: 128 x 128 x 96), at 15 with walls (3840: 128 x 120 x 128)
+    ("f64", (128, 128, 96), ""), ("f64", (129, 128, 96), ""), ("f64", (128, 120, 128), "xz"), ("f32", (128, 120, 129), "xz"),
     # FP32 marches choose their tile above 108^3 cells, walled ones run fused from 144^3
     ("f32", (108, 108, 108), ""), ("f32", (108, 108, 109), ""), ("f32", (151, 173, 129), ""), ("f32", (250, 100, 75), ""),
     ("f32", (136, 141, 139), "xz"), ("f32", (144, 144, 144), "y"), ("f64", (128, 128, 128), ""),
