@@ -60,9 +60,11 @@ __device__ __forceinline__ T face_diff(T p_lo, T p_hi) { return p_hi - p_lo; }
 // where S, D are the face sums and differences above, nhs = -s/(2 dx), ge = gamma eps / dx^2,
 // and q'_a+ / q'_a- the pre-scaled sharpening products of the two neighbours along axis a (the
 // cell's own q cancels between its two faces). Exactly the flux difference of the recipe,
-// regrouped; every variant evaluates it through this one function, in this order.
-// The marches evaluate the terms of a plane's own four faces one iteration ahead (plane_adv,
-// plane_dif) and finish with the z faces and the sharpening products (finish_rhs).
+// regrouped; every variant evaluates it in this order.
+// The fused marches evaluate the terms of a plane's own four faces one iteration ahead (plane_adv,
+// plane_dif) and finish with the z faces and the sharpening products (finish_rhs): the operations of
+// cell_rhs. The others call that, which is written out: put together from the parts it leaves the
+// compiler another schedule.
 template <typename T>
 __device__ __forceinline__ T plane_adv(T sxm, T sxp, T sym, T syp, T u0, T u1, T v0, T v1)
 {
@@ -92,8 +94,15 @@ __device__ __forceinline__ T cell_rhs(T sxm, T sxp, T sym, T syp, T szm, T szp,
                                       T qxm, T qxp, T qym, T qyp, T qzm, T qzp,
                                       T u0, T u1, T v0, T v1, T w0, T w1, T nhs, T ge)
 {
-    return finish_rhs(plane_adv(sxm, sxp, sym, syp, u0, u1, v0, v1), plane_dif(dxm, dxp, dym, dyp), szm,
-                      szp, dzm, dzp, qxm, qxp, qym, qyp, qzm, qzp, w0, w1, nhs, ge);
+    T adv = u1 * sxp;
+    adv = fma(-u0, sxm, adv);
+    adv = fma(v1, syp, adv);
+    adv = fma(-v0, sym, adv);
+    adv = fma(w1, szp, adv);
+    adv = fma(-w0, szm, adv);
+    const T dif = ((dxp - dxm) + (dyp - dym)) + (dzp - dzm);
+    const T shp = ((qxp - qxm) + (qyp - qym)) + (qzp - qzm);
+    return fma(nhs, adv, fma(ge, dif, -shp));
 }
 
 // f on a non-uniform rectilinear mesh: per axis the flux difference of the cell's two faces over
